@@ -13,6 +13,8 @@
 //   T_j = sum over the later stages of the path; w = rank-th smallest T_j (rank = ceil(lambda*M)).
 #include "pard_device.hpp"
 
+#include <type_traits>
+
 namespace pard {
 
 namespace {
@@ -44,7 +46,8 @@ __device__ __forceinline__ int32_t snapshot_in(const int32_t* snap_ptr, int32_t 
 // A workgroup counts 4096 consecutive requests.  They belong to a contiguous range of
 // snapshots; when that range's (snapshot, stage) pairs fit the LDS counters, counting happens
 // there (each counter replicated so that the lanes of a wave spread over copies) and only
-// the non-zero sums go to global memory.
+// the non-zero sums go to global memory.  Bound by the loads: a thread issues its chunk's four 16-byte loads before it
+// counts any (33.5 M requests: 42 -> 27 us, one 4-byte load at a time before).
 __global__ __launch_bounds__(kQThreads) void queue_lengths_kernel(int32_t K, int32_t S, int64_t n, const int32_t* stage,
                                                                   const int32_t* snap_ptr, int32_t* qlen) {
     __shared__ uint32_t bins[kQBins];
@@ -52,6 +55,7 @@ __global__ __launch_bounds__(kQThreads) void queue_lengths_kernel(int32_t K, int
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * kQChunk;
     const int64_t end = base + kQChunk < n ? base + kQChunk : n;
+    const bool vec = (reinterpret_cast<uintptr_t>(stage) & 15) == 0;
     if (tid == 0) {
         s_range[0] = snapshot_in(snap_ptr, 0, K - 1, base);
         s_range[1] = snapshot_in(snap_ptr, 0, K - 1, end - 1);
@@ -64,11 +68,26 @@ __global__ __launch_bounds__(kQThreads) void queue_lengths_kernel(int32_t K, int
     if (local) while (copies < 32 && (int64_t)copies * 2 * window <= kQBins) copies *= 2;
     if (local) for (int i = tid; i < copies * (int)window; i += kQThreads) bins[i] = 0;
     __syncthreads();
-    for (int64_t r = base + tid; r < end; r += kQThreads) {
-        const int32_t u = snapshot_in(snap_ptr, u_lo, u_hi, r);
-        const int32_t s = clamp_stage(stage[r], S);
+    auto count = [&](int64_t r, int32_t raw) {
+        const int32_t u = u_lo == u_hi ? u_lo : snapshot_in(snap_ptr, u_lo, u_hi, r);
+        const int32_t s = clamp_stage(raw, S);
         if (local) atomicAdd(&bins[((u - u_lo) * S + s) * copies + (tid & (copies - 1))], 1u);
         else atomicAdd(&qlen[(int64_t)u * S + s], 1);
+    };
+    if (vec && base + kQChunk <= n) {                  // a whole chunk: 16-byte loads, all of them issued first
+        int4 v[kQChunk / (4 * kQThreads)];
+#pragma unroll
+        for (int i = 0; i < kQChunk / (4 * kQThreads); ++i) v[i] = reinterpret_cast<const int4*>(stage + base)[i * kQThreads + tid];
+#pragma unroll
+        for (int i = 0; i < kQChunk / (4 * kQThreads); ++i) {
+            const int64_t r = base + 4 * (i * kQThreads + tid);
+            count(r, v[i].x);
+            count(r + 1, v[i].y);
+            count(r + 2, v[i].z);
+            count(r + 3, v[i].w);
+        }
+    } else {
+        for (int64_t r = base + tid; r < end; r += kQThreads) count(r, stage[r]);
     }
     __syncthreads();
     if (local)
@@ -77,6 +96,37 @@ __global__ __launch_bounds__(kQThreads) void queue_lengths_kernel(int32_t K, int
             for (int c = 0; c < copies; ++c) sum += bins[g * copies + c];
             if (sum) atomicAdd(&qlen[(int64_t)u_lo * S + g], (int32_t)sum);
         }
+}
+
+// Few requests in all: one workgroup per snapshot counts its requests and stores, so nothing has to be cleared before (a
+// launch less; from here on a single snapshot could hold more than one workgroup reads in the time of that launch).
+constexpr int kQSmall = 16384;                         // requests in all, so of one snapshot too
+constexpr int kQSmallSnapshots = 4096;
+__global__ __launch_bounds__(kQThreads) void queue_lengths_small_kernel(int32_t S, int64_t n, const int32_t* stage, const int32_t* snap_ptr,
+                                                                        int32_t* qlen) {
+    constexpr int kCopies = 16;                        // the lanes of a wave spread over copies of a counter
+    __shared__ uint32_t bins[PARD_MAX_STAGES * kCopies];
+    const int tid = threadIdx.x;
+    const int32_t u = blockIdx.x;
+    for (int i = tid; i < S * kCopies; i += kQThreads) bins[i] = 0;
+    int64_t lo = snap_ptr[u], hi = snap_ptr[u + 1];
+    lo = lo < 0 ? 0 : lo;
+    hi = hi > n ? n : hi;
+    __syncthreads();
+    for (int64_t r0 = lo + tid; r0 < hi; r0 += 4 * kQThreads) {
+        int32_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = r0 + i * kQThreads < hi ? stage[r0 + i * kQThreads] : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (r0 + i * kQThreads < hi) atomicAdd(&bins[clamp_stage(v[i], S) * kCopies + (tid & (kCopies - 1))], 1u);
+    }
+    __syncthreads();
+    if (tid < S) {
+        uint32_t sum = 0;
+        for (int c = 0; c < kCopies; ++c) sum += bins[tid * kCopies + c];
+        qlen[(int64_t)u * S + tid] = (int32_t)sum;
+    }
 }
 
 // ---- downstream latency ----------------------------------------------------------------
@@ -136,20 +186,299 @@ __global__ __launch_bounds__(256) void sub_simple_kernel(SubArgs A, int64_t item
     if (v) atomicMax(&A.sub[(int64_t)u * P.S + k], (unsigned long long)v);
 }
 
+constexpr int kTThreads = 512;
+constexpr int kTUnroll = 4;                             // samples of a thread in flight
+constexpr int kTBlock = kTThreads * kTUnroll;
+
+// Samples per stage in `drawn`, padded with arrivals at 0 so that sub_tails_kernel needs no bounds inside its loop.  An
+// arrival at 0 waits 0, the least there is, so the padding shifts the order statistic by its count and nothing else.
+__host__ __device__ __forceinline__ uint32_t tails_column(uint32_t M) { return (M + kTBlock - 1) / kTBlock * kTBlock; }
+static_assert(kMaxWaitSamples % kTBlock == 0, "the padded columns fit the plan's scratch");
+
 // The arrival every (sample, stage) pair draws depends on neither the snapshot nor the path:
 // gather them once per call, stage-major, so that the per-path kernel below reads them with
 // unit stride instead of chasing two dependent random loads per pair.
 __global__ __launch_bounds__(256) void drawn_arrivals_kernel(int32_t S, uint32_t M, const int32_t* samples, const uint32_t* picks,
-                                                             uint32_t m_mul, uint32_t m_shf, uint32_t* drawn) {
+                                                             uint32_t m_mul, uint32_t m_shf, uint32_t* drawn, uint32_t column,
+                                                             unsigned long long* zero, int64_t zeros) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;       // t = j * S + i, the layout of picks
-    if (t >= (int64_t)M * S) return;
-    const uint32_t pick = picks[t];
-    const int32_t a = samples[pick - magic_div_dev(pick, m_mul, m_shf) * M];
+    for (int64_t i = t; i < zeros; i += (int64_t)gridDim.x * blockDim.x) zero[i] = 0ull;     // results combined by atomics
+    if (t >= (int64_t)column * S) return;
+    int32_t a = 0;
+    if (t < (int64_t)M * S) {
+        const uint32_t pick = picks[t];
+        a = samples[pick - magic_div_dev(pick, m_mul, m_shf) * M];
+    }
     const uint32_t j = (uint32_t)(t / S), i = (uint32_t)(t - (int64_t)j * S);
-    drawn[(int64_t)i * M + j] = a > 0 ? (uint32_t)a : 0u;
+    drawn[(int64_t)i * column + j] = a > 0 ? (uint32_t)a : 0u;
 }
 
-// The sampled variant: one workgroup per (snapshot, path entry).
+// The sampled variant for pipelines of at most 8 stages: one workgroup per snapshot (several for a few snapshots).
+// The value of a path behind stage k depends on the stages behind k alone, and the stages of a path are a set (a DAG
+// has one order for it), so the different ones of a snapshot are at most 255 eight-bit masks however many paths there
+// are.  Of those a stage only needs the ones whose bounds reach the largest lower bound: sum(q+d) <= value <=
+// sum(q+d) + sum d, since a wait is shorter than the duration it waits for (overload: one or two of a stage's paths).
+// What is left is evaluated together, up to eight masks at a time: the sample's waits are formed once per stage
+// (w = -a mod d) and summed per mask; one LDS histogram per mask counts 10-bit digits from the top of the mask's
+// sum d, and one wave per mask finds the digit of the rank-th smallest.  The samples are read and their waits formed
+// again for the next digit (two rounds up to sum d = 2^20), which costs less than keeping M x 8 of them: at 8 waves
+// per SIMD a thread has 64 registers.  Bound by the vector ALU (about 7 instructions per wait, 4-6 per sum, and the
+// LDS atomics).  4096 snapshots x 10,000 samples, 6 stages: 0.19 ms, one workgroup per path took 0.80.
+constexpr int kTStages = 8;
+constexpr int kTMasks = 1 << kTStages;
+constexpr int kTBatch = kTThreads / kWave;             // masks evaluated at a time, one wave to search each histogram
+constexpr int kTBits = 10;
+constexpr int kTBins = 1 << kTBits;
+constexpr int kTEntries = 2 * kTBins;                  // path entries that fit where e_stage and e_end lie (8 stages: 255 paths of 8 at most)
+
+struct TailLds {
+    uint32_t hist[kTBatch][kTBins];
+    unsigned long long value[kTMasks];                 // summed cost of the mask's stages; plus the quantile once known
+    uint32_t dur[kTMasks];                             // summed duration of the mask's stages
+    uint32_t reach[kTStages][kTMasks / 32];            // the masks behind each stage
+    unsigned long long most[kTStages];                 // largest lower bound of each stage
+    unsigned long long stage_cost[kTStages];
+    uint32_t d[kTStages], mul[kTStages], shf[kTStages];
+    float rcp[kTStages];
+    unsigned long long needed[kTMasks / 64];
+    uint32_t list[kTMasks];
+    uint32_t prefix[kTBatch], rank[kTBatch];
+    int32_t hi[kTBatch];                               // low bits of the mask's result still open
+};
+
+// Largest value[] over the masks behind stage k (0 if there are none), in every lane of the calling wave.
+__device__ __forceinline__ unsigned long long most_behind(const TailLds& L, int k, int lane) {
+    unsigned long long v = 0;
+#pragma unroll
+    for (int i = 0; i < kTMasks / 64; ++i) {
+        const int m = i * 64 + lane;
+        if ((L.reach[k][m >> 5] >> (m & 31)) & 1u) v = v > L.value[m] ? v : L.value[m];
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const unsigned long long o = __shfl_xor(v, off);
+        v = v > o ? v : o;
+    }
+    return v;
+}
+
+__global__ __launch_bounds__(kTThreads, 8) void sub_tails_kernel(SubArgs A, int32_t groups) {
+    __shared__ __align__(16) TailLds L;
+    const PlanDev& P = A.plan;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t u = (int32_t)(blockIdx.x / (unsigned)groups), group = (int32_t)(blockIdx.x % (unsigned)groups);
+    const int S = P.S;                                          // <= kTStages
+    const uint32_t M = tails_column((uint32_t)A.num_samples);   // a multiple of kTBlock, see there
+    // The path entries come into LDS first (where the histograms are later), walked there: in memory the walk is a chain
+    // of dependent loads.  The first wave meanwhile works out the stages.
+    uint8_t* e_stage = reinterpret_cast<uint8_t*>(&L.hist[0][0]);
+    uint16_t* e_end = reinterpret_cast<uint16_t*>(&L.hist[1][0]);
+    const int32_t e_lo = P.dag_entry_ptr[P.shared ? 0 : u], entries = P.dag_entry_ptr[(P.shared ? 0 : u) + 1] - e_lo;   // <= kTEntries
+    for (int32_t e = tid - 64; e >= 0 && e < entries; e += kTThreads - 64) {
+        e_stage[e] = (uint8_t)P.entry_stage[e_lo + e];
+        e_end[e] = (uint16_t)(P.entry_end[e_lo + e] - e_lo);
+    }
+    if (tid < kTStages * (kTMasks / 32)) (&L.reach[0][0])[tid] = 0u;
+    if (tid < kTStages) {
+        uint64_t c = 0;
+        uint32_t d = 0;
+        if (tid < S) stage_terms(P, u, tid, A.qlen, A.qdelay, c, d);
+        L.stage_cost[tid] = c;
+        L.d[tid] = d;
+        L.rcp[tid] = d > 0 ? 1.0f / (float)d : 0.0f;
+        // multiply-high constants for x mod d (Granlund & Montgomery, N = 32), for the durations the short form leaves out
+        uint32_t mul = 0, shf = 0;
+        if (d > 0 && (d < (1u << 10) || d >= (1u << 24))) {
+            const uint32_t l = d > 1 ? 32u - (uint32_t)__clz((int)(d - 1u)) : 0u;      // ceil(log2 d)
+            mul = (uint32_t)(wide_div((((uint64_t)1 << l) - d) << 32, d) + 1u);
+            shf = (l < 1u ? l : 1u) | ((l > 0u ? l - 1u : 0u) << 8);
+        }
+        L.mul[tid] = mul;
+        L.shf[tid] = shf;
+    }
+    __syncthreads();
+    if (tid < kTMasks) {
+        unsigned long long c = 0;
+        uint32_t d = 0;
+#pragma unroll
+        for (int s = 0; s < kTStages; ++s)
+            if ((tid >> s) & 1) { c += L.stage_cost[s]; d += L.d[s]; }
+        L.value[tid] = c;
+        L.dur[tid] = d;
+    }
+    for (int32_t e = tid; e < entries; e += kTThreads) {
+        uint32_t m = 0;
+        for (int t = e + 1; t < e_end[e]; ++t) m |= 1u << (e_stage[t] & (kTStages - 1));
+        if (m) atomicOr(&L.reach[e_stage[e] & (kTStages - 1)][m >> 5], 1u << (m & 31));
+    }
+    __syncthreads();
+    L.most[wave] = most_behind(L, wave, lane);                  // kTBatch == kTStages waves
+    __syncthreads();
+    for (int i = tid; i < kTBatch * kTBins / 4; i += kTThreads) reinterpret_cast<uint4*>(&L.hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+    bool need = false;
+    if (tid < kTMasks) {
+        for (int k = 0; k < S; ++k)
+            need |= ((L.reach[k][tid >> 5] >> (tid & 31)) & 1u) && L.value[tid] + L.dur[tid] > L.most[k];
+        const unsigned long long b = __ballot(need);
+        if (lane == 0) L.needed[wave] = b;
+    }
+    __syncthreads();
+    int count = 0;
+    {
+        int before = 0;
+#pragma unroll
+        for (int i = 0; i < kTMasks / 64; ++i) {
+            const int c = __popcll(L.needed[i]);
+            if (i < wave) before += c;
+            count += c;
+        }
+        if (need) {
+            const int at = before + __popcll(L.needed[wave] & ((1ull << lane) - 1ull));
+            if (at % groups == group) L.list[at / groups] = (uint32_t)tid;
+        }
+        count = count > group ? (count - group + groups - 1) / groups : 0;      // this workgroup's share
+    }
+    __syncthreads();
+    for (int first = 0; first < count; first += kTBatch) {
+        const int batch = count - first < kTBatch ? count - first : kTBatch;
+        uint32_t all = 0;
+        for (int t = 0; t < batch; ++t) all |= L.list[first + t];
+        all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+        if (tid < kTBatch) {
+            L.prefix[tid] = 0u;
+            L.rank[tid] = (uint32_t)A.rank + (M - (uint32_t)A.num_samples);
+            L.hi[tid] = tid < batch ? 32 - __clz((int)(L.dur[L.list[first + tid]] | 1u)) : 0;
+        }
+        __syncthreads();
+        for (int round = 0;; ++round) {
+            int open = 0;
+#pragma unroll
+            for (int t = 0; t < kTBatch; ++t) open |= L.hi[t];
+            if (__builtin_amdgcn_readfirstlane(open) == 0) break;
+            // what the round knows of every mask and stage, in scalar registers
+            uint32_t conf[kTBatch], below[kTBatch], d[kTStages];
+            float rcp[kTStages];
+#pragma unroll
+            for (int t = 0; t < kTBatch; ++t) {
+                const int hi = __builtin_amdgcn_readfirstlane(L.hi[t]);
+                const int shift = hi > kTBits ? hi - kTBits : 0;
+                const uint32_t m = hi > 0 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)L.list[first + t]) : 0u;
+                conf[t] = m | (uint32_t)shift << 8 | (uint32_t)(hi - shift) << 16;          // m = 0: nothing (more) to do
+                below[t] = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.prefix[t]) << (hi - shift);
+            }
+#pragma unroll
+            for (int s = 0; s < kTStages; ++s) {
+                d[s] = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.d[s]);
+                rcp[s] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(L.rcp[s])));
+            }
+            auto count_block = [&](uint32_t j0, auto later_round) {
+                uint32_t w[kTStages][kTUnroll];
+                uint32_t some = all;
+                asm volatile("" : "+s"(some));      // tested where it is used: the compiler would keep 72 loop-invariant conditions
+#pragma unroll
+                for (int s = 0; s < kTStages; ++s) {
+                    if (!((some >> s) & 1u)) continue;
+                    const uint32_t* col = A.drawn + s * M;
+#pragma unroll
+                    for (int x = 0; x < kTUnroll; ++x) w[s][x] = col[j0 + x * kTThreads];
+                }
+#pragma unroll
+                for (int s = 0; s < kTStages; ++s) {
+                    if (!((some >> s) & 1u)) continue;
+                    if (d[s] >= (1u << 10) && d[s] < (1u << 24)) {
+                        // w = q*d - a with q = floor(a * (1/d) + 1/2): a/d < 2^21, and conversion, reciprocal and the
+                        // fused sum together are off by less than 2^21 * 3 * 2^-24 = 0.375, so w lies in
+                        // (-0.875 d, 0.875 d] and one correction brings it into [0, d)
+#pragma unroll
+                        for (int x = 0; x < kTUnroll; ++x) {
+                            const uint32_t q = (uint32_t)fmaf((float)w[s][x], rcp[s], 0.5f);
+                            const uint32_t v = __umul24(q, d[s]) - w[s][x];
+                            w[s][x] = v < v + d[s] ? v : v + d[s];
+                        }
+                    } else if (d[s] > 0) {
+                        const uint32_t mul = L.mul[s], shf = L.shf[s];
+#pragma unroll
+                        for (int x = 0; x < kTUnroll; ++x) {
+                            const uint32_t rem = w[s][x] - magic_div_dev(w[s][x], mul, shf) * d[s];
+                            w[s][x] = rem ? d[s] - rem : 0u;
+                        }
+                    } else {
+#pragma unroll
+                        for (int x = 0; x < kTUnroll; ++x) w[s][x] = 0u;
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < kTBatch; ++t) {
+                    uint32_t c = conf[t];
+                    asm volatile("" : "+s"(c));
+                    if (!(c & (kTMasks - 1))) continue;
+                    uint32_t total[kTUnroll];
+#pragma unroll
+                    for (int x = 0; x < kTUnroll; ++x) total[x] = 0u;
+#pragma unroll
+                    for (int s = 0; s < kTStages; ++s) {
+                        if (!((c >> s) & 1u)) continue;
+#pragma unroll
+                        for (int x = 0; x < kTUnroll; ++x) total[x] += w[s][x];
+                    }
+                    const uint32_t shift = (c >> 8) & 0xFFu;
+                    uint32_t* hist = &L.hist[t][0];
+#pragma unroll
+                    for (int x = 0; x < kTUnroll; ++x) {
+                        if (later_round) {
+                            const uint32_t bin = (total[x] >> shift) - below[t];
+                            if (bin < (1u << (c >> 16))) atomicAdd(&hist[bin], 1u);
+                        } else {
+                            atomicAdd(&hist[total[x] >> shift], 1u);        // below 2^hi, the digit's own range
+                        }
+                    }
+                }
+            };
+            if (round == 0) for (uint32_t j0 = tid; j0 < M; j0 += kTBlock) count_block(j0, std::false_type{});
+            else for (uint32_t j0 = tid; j0 < M; j0 += kTBlock) count_block(j0, std::true_type{});
+            __syncthreads();
+            if (wave < batch && L.hi[wave] > 0) {               // one wave per histogram, 16 counters a lane
+                const int hi = L.hi[wave];
+                const int shift = hi > kTBits ? hi - kTBits : 0;
+                const uint32_t rank = L.rank[wave], prefix = L.prefix[wave];
+                uint4* own = reinterpret_cast<uint4*>(&L.hist[wave][lane * (kTBins / 64)]);
+                uint32_t h[kTBins / 64], mine = 0;
+#pragma unroll
+                for (int i = 0; i < kTBins / 256; ++i) {
+                    const uint4 v = own[i];
+                    own[i] = make_uint4(0, 0, 0, 0);            // ready for the next round
+                    h[4 * i] = v.x; h[4 * i + 1] = v.y; h[4 * i + 2] = v.z; h[4 * i + 3] = v.w;
+                    mine += v.x + v.y + v.z + v.w;
+                }
+                const uint32_t before = wave_inclusive_sum(mine) - mine;
+                if (rank > before && rank <= before + mine) {   // exactly one lane
+                    uint32_t run = before, bin = 0, under = before;
+#pragma unroll
+                    for (int i = 0; i < kTBins / 64; ++i) {
+                        if (rank > run && rank <= run + h[i]) { bin = (uint32_t)(lane * (kTBins / 64) + i); under = run; }
+                        run += h[i];
+                    }
+                    L.prefix[wave] = (prefix << (hi - shift)) | bin;
+                    L.rank[wave] = rank - under;
+                }
+                if (lane == 0) L.hi[wave] = shift;
+            }
+            __syncthreads();
+        }
+        if (tid < batch) L.value[L.list[first + tid]] += L.prefix[tid];
+        __syncthreads();
+    }
+    if (wave < S) {
+        unsigned long long v = most_behind(L, wave, lane);
+        if (v > kSubCap) v = kSubCap;
+        if (lane == 0) {
+            if (groups == 1) A.sub[(int64_t)u * S + wave] = v;
+            else if (v) atomicMax(&A.sub[(int64_t)u * S + wave], v);
+        }
+    }
+}
+
+// More than 8 stages: one workgroup per (snapshot, path entry).
 constexpr int kWThreads = 512;
 constexpr int kWWaves = kWThreads / kWave;
 constexpr int kWUnroll = 8;                            // samples a thread works on at once
@@ -543,6 +872,10 @@ hipError_t launch_set_modes(StageRec* recs, const int32_t* modes, int64_t count,
 hipError_t launch_queue_lengths(const PlanDev& plan, int64_t n, const int32_t* stage, const int32_t* snap_ptr,
                                 int32_t* qlen, hipStream_t stream) {
     const int64_t segs = (int64_t)plan.K * plan.S;
+    if (n <= kQSmall && plan.K <= kQSmallSnapshots && plan.K > 0) {
+        queue_lengths_small_kernel<<<(unsigned)plan.K, kQThreads, 0, stream>>>(plan.S, n, stage, snap_ptr, qlen);
+        return hipGetLastError();
+    }
     int zb = (int)((segs + 255) / 256);
     if (zb > 1024) zb = 1024;
     fill_zero32_kernel<<<zb, 256, 0, stream>>>(qlen, segs);
@@ -556,20 +889,29 @@ hipError_t launch_queue_lengths(const PlanDev& plan, int64_t n, const int32_t* s
 hipError_t launch_sub_latency(const SubArgs& a, hipStream_t stream) {
     const PlanDev& P = a.plan;
     const int64_t segs = (int64_t)P.K * P.S;
-    int zb = (int)((segs + 255) / 256);
-    if (zb > 1024) zb = 1024;
-    fill_zero_kernel<<<zb, 256, 0, stream>>>(a.sub, segs);
+    const bool tails = a.variant == PARD_SUB_FULL && P.S <= kTStages && P.max_entries_per_dag <= kTEntries;
+    // A workgroup per snapshot fills the chip from about a thousand snapshots on; below that the paths of a snapshot
+    // are dealt out to up to eight (70 snapshots: the whole planner step 21 us; 35 path by path).
+    const int32_t groups = P.K > 0 ? (P.K >= 1024 ? 1 : 1024 / P.K > 8 ? 8 : 1024 / P.K) : 1;
+    if (a.variant != PARD_SUB_FULL) {                           // (the sampled variant's first kernel does it)
+        int zb = (int)((segs + 255) / 256);
+        if (zb > 1024) zb = 1024;
+        fill_zero_kernel<<<zb, 256, 0, stream>>>(a.sub, segs);
+    }
     if (a.variant == PARD_SUB_BACK) return hipGetLastError();
     const int64_t items = P.shared ? (int64_t)P.K * P.max_entries_per_dag : P.total_entries;
-    if (items <= 0) return hipGetLastError();
+    if (items <= 0) return hipGetLastError();       // no snapshot
     if (a.variant != PARD_SUB_FULL) {
         sub_simple_kernel<<<(unsigned)((items + 255) / 256), 256, 0, stream>>>(a, items);
     } else {
         const Magic32 mm = magic_u32((uint32_t)a.num_samples);
-        const int64_t pairs = (int64_t)a.num_samples * P.S;
+        const uint32_t column = tails ? tails_column((uint32_t)a.num_samples) : (uint32_t)a.num_samples;
+        const int64_t pairs = (int64_t)column * P.S;
         drawn_arrivals_kernel<<<(unsigned)((pairs + 255) / 256), 256, 0, stream>>>(P.S, (uint32_t)a.num_samples, a.samples, a.picks,
-                                                                                  mm.m, mm.sh, a.drawn);
-        sub_quantile_kernel<<<(unsigned)items, kWThreads, (size_t)a.num_samples * 4, stream>>>(a);
+                                                                                  mm.m, mm.sh, a.drawn, column, a.sub,
+                                                                                  tails && groups == 1 ? 0 : segs);
+        if (tails) sub_tails_kernel<<<(unsigned)(P.K * groups), kTThreads, 0, stream>>>(a, groups);
+        else sub_quantile_kernel<<<(unsigned)items, kWThreads, (size_t)a.num_samples * 4, stream>>>(a);
     }
     return hipGetLastError();
 }
