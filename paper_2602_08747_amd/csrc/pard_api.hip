@@ -114,7 +114,8 @@ int pard_plan_create(pard_plan_t** out, const pard_plan_desc_t* desc) {
     const int64_t b_edg = align256((int64_t)h.entry_dag.size() * 4 + 4);
     const int64_t b_drw = align256((int64_t)PARD_MAX_WAIT_SAMPLES * h.S * 4);
     const int64_t b_spl = align256((int64_t)h.split_in.size() * 8);
-    const int64_t total = b_recs + b_lat + b_dep + b_est + b_een + b_edg + 2 * b_spl + b_drw;
+    const int64_t b_top = align256((int64_t)h.topo.size() * 4);
+    const int64_t total = b_top + b_recs + b_lat + b_dep + b_est + b_een + b_edg + 2 * b_spl + b_drw;
     if (hipGetDevice(&p->device) != hipSuccess || hipMalloc(&p->blob, (size_t)total) != hipSuccess) {
         (void)hipGetLastError();
         delete p;
@@ -136,8 +137,9 @@ int pard_plan_create(pard_plan_t** out, const pard_plan_desc_t* desc) {
     char* d_edg = put(h.entry_dag.data(), h.entry_dag.size() * 4, b_edg);
     char* d_spi = put(h.split_in.data(), h.split_in.size() * 8, b_spl);
     char* d_spw = put(h.split_whole.data(), h.split_whole.size() * 8, b_spl);
+    char* d_top = put(h.topo.data(), h.topo.size() * 4, b_top);
     p->drawn = reinterpret_cast<uint32_t*>(base + off);
-    if (!d_recs || !d_lat || !d_dep || !d_est || !d_een || !d_edg || !d_spi || !d_spw) {
+    if (!d_top || !d_recs || !d_lat || !d_dep || !d_est || !d_een || !d_edg || !d_spi || !d_spw) {
         (void)hipGetLastError();
         (void)hipFree(p->blob);
         delete p;
@@ -161,6 +163,7 @@ int pard_plan_create(pard_plan_t** out, const pard_plan_desc_t* desc) {
     d.entry_stage = reinterpret_cast<const int32_t*>(d_est);
     d.entry_end = reinterpret_cast<const int32_t*>(d_een);
     d.entry_dag = reinterpret_cast<const int32_t*>(d_edg);
+    d.topo = reinterpret_cast<const uint32_t*>(d_top);
     d.split_in = reinterpret_cast<const int64_t*>(d_spi);
     d.split_whole = reinterpret_cast<const int64_t*>(d_spw);
     d.total_entries = (int64_t)h.entry_stage.size();

@@ -24,6 +24,7 @@ struct PlanDev {
     const int32_t* entry_stage;        // [E]
     const int32_t* entry_end;          // [E]
     const int32_t* entry_dag;          // [E]
+    const uint32_t* topo;              // [D*S*2] order of the stages for a maximum over paths, S <= kTopoStages (see HostPlan)
     const int64_t* split_in;           // [D*S] per-module SLO split: longest way in (see HostPlan)
     const int64_t* split_whole;        // [D*S] longest whole path through the stage
     int64_t total_entries;             // E

@@ -61,6 +61,8 @@ inline uint32_t magic_div(uint32_t n, Magic32 k) {
     return (t + ((n - t) >> (k.sh & 0xFF))) >> (k.sh >> 8);
 }
 
+constexpr int32_t kTopoStages = 16;
+
 struct HostPlan {
     int32_t K = 0, S = 0, shared = 1, D = 0;
     bool any_fcfs = false;
@@ -80,6 +82,10 @@ struct HostPlan {
     // Per-module SLO split (Section 5.1, Clipper++): summed execution durations lat[B] along the longest way from a
     // source to a stage (the stage included) and along the longest whole path through it.
     std::vector<int64_t> split_in, split_whole;   // [D*S]
+    // Pipelines of at most kTopoStages stages: the stages by rising longest way to a sink (so successors have lower
+    // places), two words per (DAG, place p): stage at p | place of stage p << 8 | places of its next stages << 16, and the
+    // places of all its later stages.  Empty otherwise.
+    std::vector<uint32_t> topo;             // [D*S*2]
     bool split_fits = true;                 // every such sum is below 2^30 (products with 33-bit times fit 64 bits)
     bool short_form_everywhere = true;      // every stage is kStageFast with latB / W < 2^17: wait + execution of a
                                             // short queue fit 32 bits without a carry
@@ -210,6 +216,31 @@ inline int build_host_plan(const pard_plan_desc_t* d, HostPlan& hp) {
                     if (total - run > out[v]) out[v] = total - run;
                 }
                 first = end;
+            }
+            if (S <= kTopoStages) {
+                uint32_t next[kTopoStages] = {}, later[kTopoStages] = {}, height[kTopoStages] = {}, place[kTopoStages] = {};
+                for (size_t e = e0; e < e1; ++e) {
+                    const int32_t v = hp.entry_stage[e];
+                    const size_t end = (size_t)hp.entry_end[e];
+                    if (e + 1 < end) next[v] |= 1u << hp.entry_stage[e + 1];
+                    for (size_t t = e + 1; t < end; ++t) later[v] |= 1u << hp.entry_stage[t];
+                    if (end - e - 1 > height[v]) height[v] = (uint32_t)(end - e - 1);
+                }
+                for (int32_t v = 0; v < S; ++v)
+                    for (int32_t i = 0; i < S; ++i)
+                        if (height[i] < height[v] || (height[i] == height[v] && i < v)) ++place[v];
+                const size_t base = hp.topo.size();
+                hp.topo.resize(base + 2 * (size_t)S);
+                for (int32_t v = 0; v < S; ++v) {
+                    uint32_t n = 0, l = 0;
+                    for (int32_t i = 0; i < S; ++i) {
+                        n |= ((next[v] >> i) & 1u) << place[i];
+                        l |= ((later[v] >> i) & 1u) << place[i];
+                    }
+                    hp.topo[base + 2 * place[v]] |= (uint32_t)v | n << 16;
+                    hp.topo[base + 2 * place[v] + 1] = l;
+                    hp.topo[base + 2 * (size_t)v] |= place[v] << 8;
+                }
             }
             for (int32_t v = 0; v < S; ++v) {
                 hp.split_in.push_back(in[v]);
