@@ -392,6 +392,7 @@ __global__ __launch_bounds__(kCThreads) void compact_write_kernel(CompactArgs A,
 // 0.09 at 2048 and 0.14 at 1024.
 constexpr int kLThreadsMax = 512;
 constexpr int kLCap = kLThreadsMax * 16;               // queue slots the largest workgroup handles
+constexpr int kAloneQueues = 4096;                     // queues whose offsets one workgroup writes when it takes all slots
 constexpr int kLocalMin = 2048;                        // promised bounds up to here take the chained form
 static_assert(kLCap == PARD_FUSED_SNAPSHOT_CAPACITY, "per-snapshot compaction covers the on-chip snapshot size");
 
@@ -474,15 +475,20 @@ struct LocalLds {
     uint32_t wave_off[THREADS / kWave];
 };
 
-template <int THREADS>
+// ALONE: few queue slots in all, taken by one workgroup as if they were one snapshot (A.stages = all queues): the keep
+// flags, their count and the survivors in one launch instead of two or three.
+template <int THREADS, bool ALONE>
 __global__ __launch_bounds__(THREADS, 4) void compact_local_kernel(CompactArgs A, const uint32_t* kept, const uint32_t* snap_off) {
     constexpr int kLThreads = THREADS, kLWaves = THREADS / kWave;
     __shared__ LocalLds<THREADS> L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t u = blockIdx.x;
-    const uint32_t my_kept = kept[u];   // asked for together with the snapshot's bounds: what is loaded below depends on both
+    const uint32_t my_kept = ALONE ? 1u : kept[u];  // asked for together with the snapshot's bounds: what is loaded below depends on both
     int64_t a, b;
-    if (!snapshot_range(A.seg_ptr, u, A.stages, A.n, (int64_t)THREADS * 16, a, b)) return;     // reported by the counting kernel
+    if (!snapshot_range(A.seg_ptr, u, A.stages, A.n, (int64_t)THREADS * 16, a, b)) {
+        if (ALONE && tid == 0) atomicOr(A.status, kStatusSnapshotTooLarge);
+        return;                                                                                // reported by the counting kernel
+    }
     const int size = (int)(b - a);
     // a snapshot without survivors (its slice of drop[] has no zero byte) only owes its queue offsets:
     // neither its slots nor its drop bytes are read
@@ -536,7 +542,8 @@ __global__ __launch_bounds__(THREADS, 4) void compact_local_kernel(CompactArgs A
     const int64_t my_slot = tid < owned ? (int64_t)A.seg_ptr[u * A.stages + tid] - a : 0;
     // survivors of the snapshots before this one
     uint32_t before_me = 0;
-    if (snap_off) {
+    if (ALONE) {
+    } else if (snap_off) {
         before_me = tid == 0 ? snap_off[u] : 0u;
     } else {
         uint32_t x[16];                 // sixteen counts per thread (the launcher scans first when there are more): all loads in flight at once
@@ -627,12 +634,15 @@ __global__ __launch_bounds__(THREADS, 4) void compact_local_kernel(CompactArgs A
 }
 
 // After an estimate call that staged every snapshot's survivors (in queue order, from the snapshot's first
-// request's place on) and a scan of the per-snapshot counts: one wave per snapshot moves its survivors and queue
+// request's place on) and a scan of the per-snapshot counts: one workgroup per snapshot moves its survivors and queue
 // offsets to their final place.  Everything a wave needs first comes from one round of independent loads, the
-// survivors from a second one.  (Measured alternatives for 4096 snapshots: every wave adding up all earlier
-// counts itself 22 us - all waves of the device read the same few cache lines at once; 64 workgroups that add
-// them up once and move 64 snapshots each 52 us - too few, too long chains of dependent loads.)
-__global__ __launch_bounds__(kWave) void move_staged_kernel(CompactArgs A, const uint32_t* snap_off) {
+// survivors from a second one; bound by the latency of those two, so a snapshot's survivors are spread over several
+// waves (one wave took three rounds for a few thousand: 3001 snapshots of up to 8001, 31 -> 20 us).  (Measured
+// alternatives for 4096 snapshots: every wave adding up all earlier counts itself 22 us - all waves of the device read
+// the same few cache lines at once; 64 workgroups that add them up once and move 64 snapshots each 52 us - too few, too
+// long chains of dependent loads.)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void move_staged_kernel(CompactArgs A, const uint32_t* snap_off) {
     const int lane = threadIdx.x;
     const int64_t u = blockIdx.x, K = A.num_segments / A.stages;
     const int64_t a = A.seg_ptr[u * A.stages], b = A.seg_ptr[(u + 1) * A.stages];
@@ -642,13 +652,13 @@ __global__ __launch_bounds__(kWave) void move_staged_kernel(CompactArgs A, const
         (int64_t)first + mine > A.n) return;                                            // only after a broken promise
     const int32_t* __restrict__ src = A.staged + a + staging_shift(u, (uint32_t)(b - a), mine);
     int32_t* __restrict__ dst = A.surv_idx;
-    for (uint32_t i0 = 0; i0 < mine; i0 += 16 * kWave) {
+    for (uint32_t i0 = 0; i0 < mine; i0 += 16 * THREADS) {
         int32_t v[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = i0 + i * kWave + lane < mine ? __builtin_nontemporal_load(src + i0 + i * kWave + lane) : 0;
+        for (int i = 0; i < 16; ++i) v[i] = i0 + i * THREADS + lane < mine ? __builtin_nontemporal_load(src + i0 + i * THREADS + lane) : 0;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            if (i0 + i * kWave + lane < mine) __builtin_nontemporal_store(v[i], dst + first + i0 + i * kWave + lane);
+            if (i0 + i * THREADS + lane < mine) __builtin_nontemporal_store(v[i], dst + first + i0 + i * THREADS + lane);
     }
     if (lane < A.stages) A.surv_ptr[u * A.stages + lane] = (int32_t)(first + loc);
     if (u + 1 == K && lane == 0) A.surv_ptr[K * A.stages] = (int32_t)(first + mine);
@@ -674,13 +684,25 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
         compact_empty_kernel<<<(a.num_segments + 256) / 256, 256, 0, stream>>>(a.surv_ptr, a.num_segments);
         return hipGetLastError();
     }
+    // Few slots in all: one workgroup, one launch (1024 slots: 3.9 + 3.7 us in two).  Under a per-snapshot bound a snapshot
+    // that breaks the promise is skipped alone, so there only a single snapshot is taken this way.
+    if (!a.staged && a.n <= kLCap && a.num_segments <= kAloneQueues &&
+        (!compact_per_snapshot(a.max_snapshot) || (a.num_segments == a.stages && (a.max_snapshot > 4096 || a.n <= 4096)))) {
+        CompactArgs all = a;
+        all.stages = a.num_segments;
+        if (a.n <= 4096) compact_local_kernel<256, true><<<1, 256, 0, stream>>>(all, nullptr, nullptr);
+        else compact_local_kernel<512, true><<<1, 512, 0, stream>>>(all, nullptr, nullptr);
+        return hipGetLastError();
+    }
     if (compact_per_snapshot(a.max_snapshot)) {      // every snapshot fits one workgroup
         const int64_t K = a.num_segments / a.stages;
         uint32_t* kept = static_cast<uint32_t*>(a.workspace);
         uint32_t* snap_off = kept + ((K * 4 + 255) & ~(int64_t)255) / 4;
         if (a.staged) {                              // counted and staged by the estimate kernels: only the move is left
             snapshot_offsets_kernel<<<1, 1024, 0, stream>>>(a.kept, K, snap_off);
-            move_staged_kernel<<<(unsigned)K, kWave, 0, stream>>>(a, snap_off);
+            // 4096 snapshots of 4096, half kept: 64 threads 135 us for the call, 256: 128, 512: 122; of 3000: 138, 132, 135
+            if (a.max_snapshot >= 4096) move_staged_kernel<512><<<(unsigned)K, 512, 0, stream>>>(a, snap_off);
+            else move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
             return hipGetLastError();
         }
         // the smaller workgroup that covers the promised snapshot bound; up to 16 * THREADS snapshots every
@@ -690,7 +712,7 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
             const bool scan = K > 16 * THREADS;
             snapshot_kept_kernel<COUNT><<<(unsigned)K, COUNT, 0, stream>>>(a.seg_ptr, a.stages, a.n, (int64_t)THREADS * 16, a.drop, kept, a.status);
             if (scan) snapshot_offsets_kernel<<<1, 1024, 0, stream>>>(kept, K, snap_off);
-            compact_local_kernel<THREADS><<<(unsigned)K, THREADS, 0, stream>>>(a, kept, scan ? snap_off : nullptr);
+            compact_local_kernel<THREADS, false><<<(unsigned)K, THREADS, 0, stream>>>(a, kept, scan ? snap_off : nullptr);
         };
         if (a.max_snapshot <= 4096) run(std::integral_constant<int, 256>{}, std::integral_constant<int, 128>{});
         else run(std::integral_constant<int, 512>{}, std::integral_constant<int, 128>{});
