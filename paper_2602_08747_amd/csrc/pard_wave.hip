@@ -24,9 +24,12 @@
 // are in flight per compute unit.  (Measured on 131,072 snapshots of 64 requests: 0.13 ms against
 // 0.33 ms for the workgroup path; letting each wave loop over snapshots, with the next snapshot's
 // loads issued ahead and the DAG's tables parked in LDS, needed 105 registers, halved the waves
-// per SIMD and came out at 0.16 ms - the kernel issues about 560 instructions per snapshot, 320 of
-// them vector ALU, and is bound by that once enough waves hide the load latency.)
+// per SIMD and came out at 0.16 ms - the kernel issues about 540 instructions per snapshot, 290 of
+// them vector ALU, and is bound by that once enough waves hide the load latency.  Several snapshots per workgroup, a wave
+// each: the same, 80.4 us with four against 81.2.)
 #include "pard_device.hpp"
+
+#include <type_traits>
 
 namespace pard {
 
@@ -66,11 +69,82 @@ __device__ __forceinline__ void sort_words(unsigned long long (&c)[R], const int
     }
 }
 
+// The same for 32-bit words; with fewer than 64 requests only the first `lanes` (a power of two) need sorting, the others
+// hold the largest word already.  Which of its pair an element keeps is a constant of the step: a lane mask.
+constexpr unsigned long long keep_min_lanes(int r, int k, int j) {
+    unsigned long long m = 0;
+    for (int l = 0; l < kWave; ++l)
+        if (((l & j) == 0) == (((r * kWave + l) & k) == 0)) m |= 1ull << l;
+    return m;
+}
+
+template <int J>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t v) {
+    if constexpr (J == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);          // quad_perm 1,0,3,2
+    else if constexpr (J == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);     // quad_perm 2,3,0,1
+    else if constexpr (J == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);    // row_ror:8
+    else if constexpr (J < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x1F | (J << 10));
+    else return (uint32_t)__shfl_xor((int)v, J);
+}
+
+template <int R, int K, int J>
+__device__ __forceinline__ void exchange(uint32_t (&c)[R]) {
+    if constexpr (J >= kWave) {                            // partner in the same lane
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            constexpr int D = J / kWave;
+            if ((r ^ D) > r) {
+                const uint32_t a = c[r], b = c[r ^ D];
+                const bool ascending = ((r * kWave) & K) == 0;
+                c[r] = ascending ? (a < b ? a : b) : (a > b ? a : b);
+                c[r ^ D] = ascending ? (a > b ? a : b) : (a < b ? a : b);
+            }
+        }
+    } else {
+        auto one = [&](auto row) {
+            constexpr int r = decltype(row)::value;
+            const uint32_t other = from_lane_xor<J>(c[r]);
+            const uint32_t least = c[r] < other ? c[r] : other, most = c[r] < other ? other : c[r];
+            c[r] = __builtin_amdgcn_inverse_ballot_w64(keep_min_lanes(r, K, J)) ? least : most;
+        };
+        one(std::integral_constant<int, 0>{});
+        if constexpr (R > 1) one(std::integral_constant<int, 1>{});
+    }
+    if constexpr (J > 1) exchange<R, K, J / 2>(c);
+}
+
+template <int R>
+__device__ __forceinline__ void sort_words32(uint32_t (&c)[R], const int m) {
+    exchange<R, 2, 1>(c);
+    exchange<R, 4, 2>(c);
+    exchange<R, 8, 4>(c);
+    exchange<R, 16, 8>(c);
+    if (m > 16) {                                          // m is the same for all lanes
+        exchange<R, 32, 16>(c);
+        if (m > 32) {
+            exchange<R, 64, 32>(c);
+            if constexpr (R > 1) exchange<R, 128, 64>(c);
+        }
+    }
+}
+
 constexpr unsigned long long kNoRequest = ~0ull;          // sorts behind every request
 constexpr int kStageShift = 40, kKeyShift = 8;            // word = stage << 40 | key << 8 | local index
 
+// Minimum over the wave, the same in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+    auto lower = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+    v = lower(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));         // row_shr:1
+    v = lower(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));         // row_shr:2
+    v = lower(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));         // row_shr:4
+    v = lower(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));         // row_shr:8
+    v = lower(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));         // row_bcast:15
+    v = lower(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));         // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
 // LDS words (4 bytes) a snapshot of up to 64 * R requests and S stages needs.
-__host__ __device__ constexpr int wave_lds_words(int R, int S) { return kWave * R + 17 * S + 2 + kWave; }
+__host__ __device__ constexpr int wave_lds_words(int R, int S) { return (kWave * R + 17 * S + 2 + kWave + 3) & ~3; }
 
 // Lanes l of slot row r (slots r * 64 + l) with first <= r * 64 + l < end.
 __device__ __forceinline__ unsigned long long row_mask(int r, int first, int end) {
@@ -138,26 +212,66 @@ __global__ __launch_bounds__(kWave, 8) void wave_snapshot_kernel(FusedArgs A) {
     if (entries_cached && lane < n_entries)
         ent[lane] = (uint32_t)P.entry_stage[e_lo + lane] | ((uint32_t)(P.entry_end[e_lo + lane] - e_lo) << 8);
     __syncthreads();
-    unsigned long long c[R];
+    uint32_t key[R];
+    int32_t sg[R];
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int e = r * kWave + lane;
-        const int s = clamp_stage(st[r], S);
-        const int mode = P.uniform_mode >= 0 ? P.uniform_mode : (recs[s].mode & 0xFF);
+        sg[r] = clamp_stage(st[r], S);
+        const int mode = P.uniform_mode >= 0 ? P.uniform_mode : (recs[sg[r]].mode & 0xFF);
         int32_t arr = 0;
         if (mode == PARD_ORDER_FCFS && e < m) arr = A.arrival[lo + e];
-        const uint32_t k = order_key(mode, dl[r], arr);
-        c[r] = e < m ? ((unsigned long long)s << kStageShift) | ((unsigned long long)k << kKeyShift) | (unsigned)e : kNoRequest;
+        key[r] = order_key(mode, dl[r], arr);
+        if (e < m) {
+            kmin = key[r] < kmin ? key[r] : kmin;
+            kmax = key[r] > kmax ? key[r] : kmax;
+        }
         by_id[e] = (uint32_t)dl[r];
     }
 
     // ---- 2. queue order -----------------------------------------------------------------
-    sort_words<R>(c, lane);
+    // The snapshot's keys usually span few enough bits for stage, key and index to share 32 bits: then a step of the
+    // network is one exchange, a minimum, a maximum and a select, and the network stops at the next power of two of the
+    // snapshot's size.  Bound by vector instructions (288 per snapshot of up to 64 against 322 with 64-bit words; what is
+    // left is the estimate): 100,000 snapshots of up to 128 requests 160 -> 105 us with the compaction, of up to 64 91 -> 80.
+    kmin = wave_min(kmin);
+    kmax = ~wave_min(~kmax);
+    constexpr int kIdBits = R == 1 ? 6 : 7;
+    const int key_bits = kmax > kmin ? 32 - __builtin_clz(kmax - kmin) : 0;
+    int sp[R];                               // stage of slot p = r * 64 + lane; S behind the last request
+    uint32_t id[R];                          // its request's index in the snapshot
+    const int stage_bits = S > 1 ? 32 - __builtin_clz((uint32_t)S - 1u) : 0;
+    // (strictly below 32: the word of all ones is no request's)
+    if (stage_bits + key_bits + kIdBits < 32) {
+        uint32_t c[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = r * kWave + lane;
+            c[r] = e < m ? ((((uint32_t)sg[r] << key_bits) | (key[r] - kmin)) << kIdBits) | (uint32_t)e : 0xFFFFFFFFu;
+        }
+        sort_words32<R>(c, m);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            sp[r] = r * kWave + lane < m ? (int)(c[r] >> (key_bits + kIdBits)) : S;
+            id[r] = c[r] & (N - 1);
+        }
+    } else {
+        unsigned long long c[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = r * kWave + lane;
+            c[r] = e < m ? ((unsigned long long)sg[r] << kStageShift) | ((unsigned long long)key[r] << kKeyShift) | (unsigned)e : kNoRequest;
+        }
+        sort_words<R>(c, lane);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            sp[r] = r * kWave + lane < m ? (int)(c[r] >> kStageShift) : S;
+            id[r] = (uint32_t)c[r] & (N - 1);
+        }
+    }
 
     // ---- 3. queue starts: slot p opens every queue after its predecessor's up to its own -----
-    int sp[R];                               // stage of slot p = r * 64 + lane; S behind the last request
-#pragma unroll
-    for (int r = 0; r < R; ++r) sp[r] = r * kWave + lane < m ? (int)(c[r] >> kStageShift) : S;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         int prev = __shfl_up(sp[r], 1);
@@ -171,7 +285,7 @@ __global__ __launch_bounds__(kWave, 8) void wave_snapshot_kernel(FusedArgs A) {
 
     // ---- 4. full-queue costs, downstream maximum per stage ------------------------------------
     for (int i = lane; i < S; i += kWave)
-        cfull[i] = stage_cost(recs[i], (uint32_t)(seg_start[i + 1] - seg_start[i]), lat_dag + i * PARD_LAT_ENTRIES);
+        cfull[i] = stage_cost_short(recs[i], (uint32_t)(seg_start[i + 1] - seg_start[i]), lat_dag + i * PARD_LAT_ENTRIES);
     __syncthreads();
     if (A.sub) {
         for (int i = lane; i < S; i += kWave) {
@@ -196,7 +310,7 @@ __global__ __launch_bounds__(kWave, 8) void wave_snapshot_kernel(FusedArgs A) {
     }
     int32_t dq[R];                           // deadline of the request in slot p
 #pragma unroll
-    for (int r = 0; r < R; ++r) dq[r] = (int32_t)by_id[(uint32_t)c[r] & (N - 1)];   // a slot without request reads a deadline it never uses
+    for (int r = 0; r < R; ++r) dq[r] = (int32_t)by_id[id[r]];   // a slot without request reads a deadline it never uses
     __syncthreads();
 
     // ---- 5. estimate and decision per queue slot; back to request order through LDS ----------
@@ -255,9 +369,8 @@ __global__ __launch_bounds__(kWave, 8) void wave_snapshot_kernel(FusedArgs A) {
     for (int r = 0; r < R; ++r) {
         const int p = r * kWave + lane;
         if (p < m) {
-            const uint32_t id = (uint32_t)c[r] & (N - 1);
-            by_id[id] = (uint32_t)est[r] | ((uint32_t)drp[r] << 31);
-            A.order[lo + p] = (int32_t)(lo + id);
+            by_id[id[r]] = (uint32_t)est[r] | ((uint32_t)drp[r] << 31);
+            A.order[lo + p] = (int32_t)(lo + id[r]);
         }
     }
     __syncthreads();
