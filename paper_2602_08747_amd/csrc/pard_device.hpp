@@ -122,6 +122,59 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
     return v;
 }
 
+// Minimum over the lanes below (INT32_MAX in lane 0), on the vector ALU's data-parallel primitives.
+__device__ __forceinline__ int32_t wave_exclusive_min(int32_t v) {
+    const int32_t inf = kInt32Max;
+    int32_t x = __builtin_amdgcn_update_dpp(inf, v, 0x138, 0xF, 0xF, false);          // wave_shr:1: the lane below's value
+    auto lower = [](int32_t a, int32_t b) { return a < b ? a : b; };
+    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x111, 0xF, 0xF, false));         // row_shr:1
+    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x112, 0xF, 0xF, false));         // row_shr:2
+    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x114, 0xF, 0xF, false));         // row_shr:4
+    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x118, 0xF, 0xF, false));         // row_shr:8
+    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x142, 0xA, 0xF, false));         // row_bcast:15 into rows 1, 3
+    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x143, 0xC, 0xF, false));         // row_bcast:31 into rows 2, 3
+    return x;
+}
+
+// How many positions, from 0 on, a request is in time at: positions with cost <= budget, for a stage whose cost never
+// falls with the position and admits the short-queue form (pos < 2^13).  quick: the stage's row, lat: its latency table.
+// Behind the first batch the cost is floor(q lat[B] / W) + lat[B] with q = ceil(pos / B), so q < (budget - lat[B] + 1) W / lat[B]:
+// a float quotient, off by less than 0.01, and one exact comparison to either side.  In the first batch the wait is that
+// of one batch and the execution one of B table entries.
+__device__ __forceinline__ uint32_t positions_in_time(const uint32_t* quick, float inv, const uint32_t* lat, int64_t budget) {
+    if (budget < (int64_t)lat[0]) return 0u;
+    const uint32_t b = budget < 0xFFFFFFFFll ? (uint32_t)budget : 0xFFFFFFFFu;      // every cost is below 2^32
+    const uint4 qa = *reinterpret_cast<const uint4*>(quick);
+    const uint32_t bW = quick[4];
+    auto wait = [&](uint32_t q) { return __umul24(q, qa.w) + (uint32_t)(((float)__umul24(q, bW) + 0.5f) * __uint_as_float(qa.z)); };
+    const uint32_t full = lat[qa.x], first = wait(1u);
+    if (b < full || b - full < first) {                // not in time behind the whole first batch
+        if (b < first) return 1u;
+        uint32_t lo = 1u, hi = qa.x + 1u;              // table entries 1 .. B-1: the first that is too long
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (lat[mid] <= b - first) lo = mid + 1u; else hi = mid;
+        }
+        return lo;
+    }
+    const uint32_t room = b - full;                    // the longest wait that is in time
+    uint32_t q = (uint32_t)fminf(((float)room + 1.0f) * inv, 8190.0f);
+    if (wait(q) > room) --q;
+    else if (wait(q + 1u) <= room) ++q;
+    return q * (qa.x + 1u) + 1u;
+}
+
+// One step of a queue's chain under low budget first: 64 requests in queue order (`ok` in the lanes that hold one), c = how
+// many positions a request is in time at, counted from the kept requests ahead of the 64.  Budgets rise along the queue, so
+// does c, and the recurrence a' = min(a + 1, c) unrolls to a_i = min(i, i - 1 + min over i' < i of (c_i' - i')).  Returns the
+// position and the mask of kept requests.
+__device__ __forceinline__ int chain_step(bool ok, int c, int lane, unsigned long long& keep) {
+    const int32_t least = wave_exclusive_min(c - lane);        // INT32_MAX for lane 0
+    const int a = lane > 0 && least <= 0 ? lane - 1 + least : lane;
+    keep = __ballot(ok && a < c);
+    return a;
+}
+
 // Estimates and decisions are written once and not read again by the call that writes them: streaming stores
 // (they leave the caches early and do not push out what the next kernel reads).
 typedef int pard_v4i __attribute__((ext_vector_type(4)));

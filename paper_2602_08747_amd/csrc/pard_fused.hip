@@ -58,7 +58,8 @@ struct SnapshotLds {
     unsigned long long cfull[SCAP];
     unsigned long long down[SCAP];
     int32_t seg_start[SCAP + 1];
-    __align__(16) uint32_t quick[SCAP][8];   // per stage: B-1, 1/B, 1/W, aW, bW, queue start (short-queue form)
+    __align__(16) uint32_t quick[SCAP][8];   // per stage: B-1, 1/B, 1/W, aW, bW, queue start (short-queue form), W/lat[B]
+    unsigned long long ahead;                        // sequentially consistent: the queues whose positions in time are formed ahead of the walk
     uint32_t slow_stages;                            // set when some stage cannot use the short-queue form
     uint32_t wave_tot[16];
     uint32_t kept_tot[16][2];                        // survivor staging: kept slots per wave and group of loads
@@ -69,21 +70,7 @@ constexpr int log2_of(int x) { return x <= 1 ? 0 : 1 + log2_of(x / 2); }
 
 // FULL: the snapshot holds exactly kCap requests and every array is 16-byte aligned at its
 // start, so no per-request bounds test is needed.
-// Minimum over the lanes below (INT32_MAX in lane 0), on the vector ALU's data-parallel primitives.
-__device__ __forceinline__ int32_t wave_exclusive_min(int32_t v) {
-    const int32_t inf = kInt32Max;
-    int32_t x = __builtin_amdgcn_update_dpp(inf, v, 0x138, 0xF, 0xF, false);          // wave_shr:1: the lane below's value
-    auto lower = [](int32_t a, int32_t b) { return a < b ? a : b; };
-    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x111, 0xF, 0xF, false));         // row_shr:1
-    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x112, 0xF, 0xF, false));         // row_shr:2
-    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x114, 0xF, 0xF, false));         // row_shr:4
-    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x118, 0xF, 0xF, false));         // row_shr:8
-    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x142, 0xA, 0xF, false));         // row_bcast:15 into rows 1, 3
-    x = lower(x, __builtin_amdgcn_update_dpp(inf, x, 0x143, 0xC, 0xF, false));         // row_bcast:31 into rows 2, 3
-    return x;
-}
-
-template <int T, int CAP, int SCAP, bool FULL, bool CONSISTENT>
+template <int T, int CAP, int SCAP, bool FULL, bool CONSISTENT, bool AHEAD>
 __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CAP, SCAP>& L, const int u, const int64_t lo,
                                               const int m, const bool aligned, const int off) {
     constexpr int kCap = CAP;
@@ -93,6 +80,13 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
     constexpr int kAuxWords = SnapshotLds<CAP, SCAP>::kAuxWords;
     constexpr int G = kCap / (4 * T);       // groups of 4 consecutive requests per thread
     constexpr int CW = kCntWords / T;       // counter words scanned per thread
+    // AHEAD, sequentially consistent under low budget first: in how many positions a request is in time is formed by all
+    // threads side by side before a wave walks its queue; the walk, a chain of dependent steps, is then a prefix minimum per
+    // 64 requests instead of 64 estimates, a search and the minimum.  It costs instructions and saves waiting, so only the
+    // largest capacity has it, where a queue is longest: 3001 snapshots of up to 8001, three SLOs, 349 -> 291 us with the
+    // compaction, 4096 of 8192 shuffled 363 -> 352, in overload 332 -> 333, but 6000 of 3500 in overload 253 -> 287 and
+    // 10,000 of 1000 90 -> 105; and not under high budget first, whose walk needs one estimate per request (191 -> 234).
+    constexpr bool kAhead = AHEAD;
     static_assert(kCap == (1 << kIdxBits) && kCap <= PARD_FUSED_SNAPSHOT_CAPACITY, "capacity");
     static_assert(G >= 1 && CW >= 2 && CW % 2 == 0 && kCntWords % T == 0 && T % kWave == 0 && T / kWave <= 16, "shape");
 
@@ -149,7 +143,7 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
         uint32_t* dst = reinterpret_cast<uint32_t*>(L.recs);
         for (int i = tid; i < S * (int)(sizeof(StageRec) / 4); i += T) dst[i] = src[i];
         for (int i = tid; i < SCAP; i += T) L.down[i] = 0;
-        if (tid == 0) { L.red[0] = 0xFFFFFFFFu; L.red[1] = 0u; L.slow_stages = 0u; }
+        if (tid == 0) { L.red[0] = 0xFFFFFFFFu; L.red[1] = 0u; L.slow_stages = 0u; L.ahead = 0ull; }
         // cache in the (so far unused) index array: the DAG's latency tables and path entries
         for (int i = tid; i < S * PARD_LAT_ENTRIES; i += T) aux[i] = (uint32_t)lat_dag[i];
         if (entries_cached)
@@ -280,6 +274,7 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
         L.quick[tid][3] = r.aW;
         L.quick[tid][4] = r.bW;
         L.quick[tid][5] = (uint32_t)a;
+        if (AHEAD) L.quick[tid][6] = __float_as_uint(r.latB > 0 ? (float)r.W / (float)r.latB : 1.0e30f);
         if (!(r.mode & kStageFast)) L.slow_stages = 1u;
     }
     uint32_t se[G][4];                       // bucket start (13 bits) | bucket size - 1 (13 bits) | stage << 26
@@ -301,6 +296,14 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
     }
     __syncthreads();
 
+    if (kAhead && !wide) {
+        for (int k = wave; k < S; k += T / kWave) {     // one wave looks at one table
+            const uint32_t* row = aux + k * PARD_LAT_ENTRIES;
+            const bool falls = lane + 1 < L.recs[k].B && row[lane + 1] < row[lane];
+            if (__ballot(falls) == 0ull && (L.recs[k].mode & (kStageFast | 0xFF)) == (kStageFast | PARD_ORDER_LBF) && lane == 0)
+                atomicOr(&L.ahead, 1ull << k);
+        }
+    }
     // ---- 4. downstream maximum per stage over the path CSR (or as given) ---------------
     if (A.sub) {
         if (tid < S) {
@@ -384,18 +387,43 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
 
     if (CONSISTENT) {
         // ---- 5'. decisions in queue order, positions = kept requests ahead -------------------
-        // deadlines by queue slot (L.low is free: every read of the rank phase is behind the barrier above)
+        // deadlines (or the positions in time) by queue slot (L.low is free: every read of the rank phase is behind the barrier above)
+        const unsigned long long ahead_of = kAhead ? L.ahead : 0ull;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (dead_group(g)) continue;
             const int base = (g * T + tid) * 4;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (live(base + c)) L.low[se[g][c] & 0x1FFFu] = (uint32_t)dl[g][c];
+                if (live(base + c)) {
+                    uint32_t v = (uint32_t)dl[g][c];
+                    if (kAhead) {
+                        const uint32_t k = se[g][c] >> 26;
+                        if ((ahead_of >> k) & 1ull)
+                            v = dl[g][c] == kInt32Max ? 0x7FFFu
+                                                      : positions_in_time(&L.quick[k][0], __uint_as_float(L.quick[k][6]), aux + k * PARD_LAT_ENTRIES,
+                                                                          (int64_t)dl[g][c] - (int64_t)now - (int64_t)L.down[k]);
+                    }
+                    L.low[se[g][c] & 0x1FFFu] = v;
+                }
         }
         __syncthreads();
         for (int k = wave; k < S; k += T / kWave) {            // one wave per queue
             const int s0 = L.seg_start[k], s1 = L.seg_start[k + 1];
+            if ((ahead_of >> k) & 1ull) {
+                uint32_t kept = 0;                              // kept requests of this queue so far (same in every lane)
+                uint32_t next = s0 + lane < s1 ? L.low[s0 + lane] : 0u;
+                for (int first = s0; first < s1; first += kWave) {
+                    const int j = first + lane;
+                    const int c = (int)next - (int)kept;
+                    next = j + kWave < s1 ? L.low[j + kWave] : 0u;
+                    unsigned long long keep;
+                    const int a = chain_step(j < s1, c, lane, keep);
+                    if (j < s1) L.low[j] = (kept + (uint32_t)a) | (a < c ? 0u : 0x80000000u);
+                    kept += (uint32_t)__popcll(keep);
+                }
+                continue;
+            }
             const unsigned long long dn = L.down[k];
             // the DAG's latency tables sit in LDS unless the wide case took that array back
             const int32_t* lat_row = wide ? lat_dag + k * PARD_LAT_ENTRIES : reinterpret_cast<const int32_t*>(aux) + k * PARD_LAT_ENTRIES;
@@ -482,11 +510,21 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
             const int base = (g * T + tid) * 4;
             int32_t est[4];
             uint8_t drp[4];
+            if (kAhead) asm volatile("" ::: "memory");       // one group of four requests at a time (register pressure)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const uint32_t v = live(base + c) ? L.low[se[g][c] & 0x1FFFu] : 0u;
                 est[c] = (int32_t)(v & 0x7FFFFFFFu);
                 drp[c] = (uint8_t)(v >> 31);
+                const uint32_t k = se[g][c] >> 26;
+                if (kAhead && ((ahead_of >> k) & 1ull)) {    // a position so far
+                    const uint32_t pos = v & 0x7FFFFFFFu;
+                    const uint4 qa = *reinterpret_cast<const uint4*>(&L.quick[k][0]);     // B-1, 1/B, 1/W, aW
+                    const uint32_t q = (uint32_t)(((float)(pos + qa.x) + 0.5f) * __uint_as_float(qa.y));
+                    const uint32_t wait = __umul24(q, qa.w) + (uint32_t)(((float)__umul24(q, L.quick[k][4]) + 0.5f) * __uint_as_float(qa.z));
+                    const uint64_t e64 = (uint64_t)wait + aux[k * PARD_LAT_ENTRIES + (pos < qa.x ? pos : qa.x)] + L.down[k];
+                    est[c] = e64 > (uint64_t)kInt32Max ? kInt32Max : (int32_t)e64;
+                }
             }
             if (whole(base)) {
                 stream_store(reinterpret_cast<int4*>(A.est + lo_s + base), make_int4(est[0], est[1], est[2], est[3]));
@@ -644,7 +682,7 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
     if (tid == 0) A.kept[u] = total;
 }
 
-template <int T, int CAP, int SCAP, bool CONSISTENT>
+template <int T, int CAP, int SCAP, bool CONSISTENT, bool AHEAD>
 __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = CAP;
     __shared__ SnapshotLds<CAP, SCAP> L;
@@ -674,14 +712,19 @@ __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     const int shift = (int)(lo & 3);
     const bool aligned = (bits & 15) == 0 && m + shift <= kCap;
     const int off = aligned ? shift : 0;
-    if (m == kCap && aligned && off == 0) snapshot_body<T, CAP, SCAP, true, CONSISTENT>(A, L, u, lo, m, true, 0);
-    else snapshot_body<T, CAP, SCAP, false, CONSISTENT>(A, L, u, lo, m, aligned, off);
+    if (m == kCap && aligned && off == 0) snapshot_body<T, CAP, SCAP, true, CONSISTENT, AHEAD>(A, L, u, lo, m, true, 0);
+    else snapshot_body<T, CAP, SCAP, false, CONSISTENT, AHEAD>(A, L, u, lo, m, aligned, off);
 }
 
 template <int CAP, int T, int SCAP>
 void launch_stages(const FusedArgs& a, hipStream_t stream) {
-    if (a.consistent) fused_snapshot_kernel<T, CAP, SCAP, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
-    else fused_snapshot_kernel<T, CAP, SCAP, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+    if constexpr (CAP == PARD_FUSED_SNAPSHOT_CAPACITY)
+        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF) {
+            fused_snapshot_kernel<T, CAP, SCAP, true, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+            return;
+        }
+    if (a.consistent) fused_snapshot_kernel<T, CAP, SCAP, true, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+    else fused_snapshot_kernel<T, CAP, SCAP, false, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
 }
 
 template <int CAP, int T>

@@ -24,6 +24,9 @@
 //   4. per request: queue slot = sub-block's first slot of its stage + requests of that stage in
 //      earlier lanes + rank inside the lane; own-stage cost in the exact short-queue form,
 //      estimate, drop decision; outputs leave in request order, the queue order via LDS.
+//      Sequentially consistent variant (positions count the kept requests ahead): every thread first leaves, by queue
+//      slot, in how many positions its requests are in time, one wave per queue turns those into positions and decisions
+//      (a prefix minimum per 64 requests), and the estimates are formed from the positions.
 #include "pard_device.hpp"
 
 namespace pard {
@@ -46,7 +49,7 @@ constexpr int kPsStages = kPresortedMaxStages;     // 3-bit count fields of stag
 constexpr uint32_t kDeadStage = 7;
 constexpr int kPsEntries = 128;                    // path entries of a DAG kept in LDS (longer lists are read in place)
 
-template <int T>
+template <int T, bool CONS>
 struct PresortedLds {
     static constexpr int CAP = 16 * T;
     static constexpr int SUB = T / kWave * 4;                 // sub-blocks of 256 requests
@@ -64,6 +67,9 @@ struct PresortedLds {
     uint32_t disorder[T / kWave];                             // per wave: it saw a deadline fall
     uint32_t ktot[SUB];                                       // kept slots per sub-block
     uint32_t ent[kPsEntries];                                 // the DAG's path entries: stage | (end of the entry's path) << 8
+    uint16_t chain[CONS ? CAP : 1];                           // sequentially consistent, by queue slot: positions the request is in time
+                                                              // at, then its position | drop << 15
+    float inv[8];                                             // sequentially consistent: W / lat[B] per stage
     uint32_t verdict;                                         // 0: in order and finished here, 1: left to the general kernel
 };
 
@@ -73,10 +79,11 @@ __device__ __forceinline__ int32_t from_previous_lane(int32_t v, int32_t own) {
 }
 
 // FULL: the snapshot holds exactly 16 T requests and every array is 16-byte aligned at its start.
-template <int T, bool FULL>
-__device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<T>& L, const int u, const int64_t lo,
+// CONS: sequentially consistent dropping (positions count the kept requests ahead, Section 4.1).
+template <int T, bool FULL, bool CONS>
+__device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<T, CONS>& L, const int u, const int64_t lo,
                                                const int m, const bool aligned, const int off) {
-    constexpr int SUB = PresortedLds<T>::SUB;
+    constexpr int SUB = PresortedLds<T, CONS>::SUB;
     const PlanDev& P = A.plan;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -185,7 +192,15 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
             if (lane > 0) broken = L.edge_lo[lane] < L.edge_hi[lane - 1];
         }
         if (lane < T / kWave) broken |= L.disorder[lane] != 0u;
-        const bool disorder = __ballot(broken) != 0ull;
+        bool disorder = __ballot(broken) != 0ull;
+        if (CONS) {
+            // positions in time are the first so many only where the latency table never falls up to the batch size
+            for (int k = 0; k < S; ++k) {
+                const uint32_t* row = &L.lat[k * PARD_LAT_ENTRIES];
+                if (__ballot(lane + 1 < L.recs[k].B && row[lane + 1] < row[lane]) != 0ull) disorder = true;
+            }
+            if (lane < S) L.inv[lane] = L.recs[lane].latB > 0 ? (float)L.recs[lane].W / (float)L.recs[lane].latB : 1.0e30f;
+        }
         uint32_t cnt[kPsStages], pre[kPsStages];
         cnt[0] = t0 & 1023u; cnt[1] = (t0 >> 10) & 1023u; cnt[2] = (t0 >> 20) & 1023u;
         cnt[3] = t1 & 1023u; cnt[4] = (t1 >> 10) & 1023u; cnt[5] = (t1 >> 20) & 1023u;
@@ -256,6 +271,48 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     }
     if (tid == 0) A.todo[u] = 0u;
 
+    // ---- sequentially consistent: positions in time by queue slot, then every queue's chain of decisions --------
+    uint32_t place[CONS ? 8 : 1];            // two queue slots per word
+    if (CONS) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int base = wbase + j * 256;
+            const unsigned long long before = (unsigned long long)ex0[j] | ((unsigned long long)ex1[j] << 30);
+            const uint16_t* fs = &L.first_slot[wave * 4 + j][0];
+            asm volatile("" ::: "memory");   // one sub-block at a time (register pressure)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t k = (sr[j] >> (8 * c)) & 7u;
+                const uint32_t slot = (uint32_t)fs[k] + ((uint32_t)(before >> (k * 10u)) & 1023u) + ((sr[j] >> (8 * c + 3)) & 7u);
+                if (c & 1) place[2 * j + (c >> 1)] |= slot << 16; else place[2 * j + (c >> 1)] = slot;
+                if (live(base + c)) {
+                    uint32_t v = 0x7FFFu;
+                    if (dl[j][c] != kInt32Max) {
+                        const uint64_t dn = (uint64_t)L.quick[k][6] | ((uint64_t)L.quick[k][7] << 32);
+                        v = positions_in_time(&L.quick[k][0], L.inv[k], &L.lat[k * PARD_LAT_ENTRIES], (int64_t)dl[j][c] - (int64_t)now - (int64_t)dn);
+                    }
+                    L.chain[slot] = (uint16_t)(v < 0x7FFFu ? v : 0x7FFFu);
+                }
+            }
+        }
+        __syncthreads();
+        for (int k = wave; k < S; k += T / kWave) {            // one wave per queue
+            const int s0 = L.seg_start[k], s1 = L.seg_start[k + 1];
+            uint32_t kept = 0;
+            uint32_t next = s0 + lane < s1 ? L.chain[s0 + lane] : 0u;
+            for (int first = s0; first < s1; first += kWave) {
+                const int at = first + lane;
+                const int c = (int)next - (int)kept;
+                next = at + kWave < s1 ? L.chain[at + kWave] : 0u;
+                unsigned long long keep;
+                const int a = chain_step(at < s1, c, lane, keep);
+                if (at < s1) L.chain[at] = (uint16_t)((kept + (uint32_t)a) | (a < c ? 0u : 0x8000u));
+                kept += (uint32_t)__popcll(keep);
+            }
+        }
+        __syncthreads();
+    }
+
     // ---- 4. queue slot, estimate, drop decision -------------------------------------------------
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -269,17 +326,24 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint32_t k = (sr[j] >> (8 * c)) & 7u;     // slots that are not live compute on the zeroed rows of stage 7 and are discarded
-            const uint32_t slot = (uint32_t)fs[k] + ((uint32_t)(before >> (k * 10u)) & 1023u) + ((sr[j] >> (8 * c + 3)) & 7u);
+            const uint32_t slot = CONS ? (place[CONS ? 2 * j + (c >> 1) : 0] >> (16 * (c & 1))) & 0xFFFFu
+                                       : (uint32_t)fs[k] + ((uint32_t)(before >> (k * 10u)) & 1023u) + ((sr[j] >> (8 * c + 3)) & 7u);
+            const uint32_t decided = CONS ? L.chain[live(base + c) ? slot : 0u] : 0u;
             const uint4 qa = *reinterpret_cast<const uint4*>(&L.quick[k][0]);     // B-1, 1/B, 1/W, aW
             const uint4 qb = *reinterpret_cast<const uint4*>(&L.quick[k][4]);     // bW, queue start, downstream
-            const uint32_t pos = slot - qb.y;
+            const uint32_t pos = CONS ? decided & 0x7FFFu : slot - qb.y;
             const uint32_t q = (uint32_t)(((float)(pos + qa.x) + 0.5f) * __uint_as_float(qa.y));
             const uint32_t p = __umul24(q, qb.x);
             const uint32_t wait = __umul24(q, qa.w) + (uint32_t)(((float)p + 0.5f) * __uint_as_float(qa.z));
             const uint32_t seen = pos < qa.x ? pos : qa.x;
             const uint64_t dn = (uint64_t)qb.z | ((uint64_t)qb.w << 32);
             const uint64_t e64 = (uint64_t)wait + L.lat[k * PARD_LAT_ENTRIES + seen] + dn;
-            finish_request(e64, now, dl[j][c], est[c], drp[c]);
+            if (CONS) {
+                est[c] = e64 > (uint64_t)kInt32Max ? kInt32Max : (int32_t)e64;
+                drp[c] = (uint8_t)(decided >> 15);
+            } else {
+                finish_request(e64, now, dl[j][c], est[c], drp[c]);
+            }
             if (live(base + c)) {
                 L.ord[slot] = (uint16_t)((uint32_t)(base + c) | ((uint32_t)drp[c] << 15));   // local index < 2^13
                 if (A.kept && !drp[c]) atomicAdd(&L.ktot[(slot + (uint32_t)off) >> 8], 1u);     // kept slots per sub-block of the slot layout
@@ -379,10 +443,10 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
 #ifndef PARD_PS_WAVES
 #define PARD_PS_WAVES 6
 #endif
-template <int T>
+template <int T, bool CONS>
 __global__ __launch_bounds__(T, PARD_PS_WAVES) void presorted_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = 16 * T;
-    __shared__ PresortedLds<T> L;
+    __shared__ PresortedLds<T, CONS> L;
     const int u = blockIdx.x;
     const int64_t n = A.n;
     // snapshot bounds, made safe whatever snap_ptr holds
@@ -417,8 +481,8 @@ __global__ __launch_bounds__(T, PARD_PS_WAVES) void presorted_snapshot_kernel(Fu
     const int shift = (int)(lo & 3);
     const bool aligned = (bits & 15) == 0 && m + shift <= kCap;
     const int off = aligned ? shift : 0;
-    if (m == kCap && aligned && off == 0) presorted_body<T, true>(A, L, u, lo, m, true, 0);
-    else presorted_body<T, false>(A, L, u, lo, m, aligned, off);
+    if (m == kCap && aligned && off == 0) presorted_body<T, true, CONS>(A, L, u, lo, m, true, 0);
+    else presorted_body<T, false, CONS>(A, L, u, lo, m, aligned, off);
 }
 
 }  // namespace
@@ -426,18 +490,21 @@ __global__ __launch_bounds__(T, PARD_PS_WAVES) void presorted_snapshot_kernel(Fu
 // Promised bounds of at most 512 requests stay with the general kernel: the smallest workgroup here is laid out for 1024
 // requests, and below about half of that the general kernel's smaller capacities are as fast or faster (65,536
 // snapshots of 256 in queue order: 0.210 ms per call through this kernel, 0.148 through the general one; of 512:
-// 0.234 either way; 43,690 of 768: 0.181 against 0.270).
+// 0.234 either way; 43,690 of 768: 0.181 against 0.270).  Sequentially consistent: only the largest workgroup, whose gain in
+// order (4096 snapshots of 8192: 284 -> 207 us) stands against 8 us for a batch in which nothing is; with 6000 snapshots of
+// up to 3500 it was 15 us less in order and 12 more otherwise.
 bool presorted_path_covers(const FusedArgs& a) {
-    return a.todo != nullptr && a.plan.presorted_ok && !a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF &&
-           a.plan.S <= kPresortedMaxStages && a.cap > 512 && a.cap <= PARD_FUSED_SNAPSHOT_CAPACITY;
+    return a.todo != nullptr && a.plan.presorted_ok && a.plan.uniform_mode == PARD_ORDER_LBF &&
+           a.plan.S <= kPresortedMaxStages && a.cap > (a.consistent ? 4096 : 512) && a.cap <= PARD_FUSED_SNAPSHOT_CAPACITY;
 }
 
 hipError_t launch_presorted(const FusedArgs& a, hipStream_t stream) {
     const dim3 grid((unsigned)a.plan.K);
-    if (a.cap <= 1024) presorted_snapshot_kernel<64><<<grid, dim3(64), 0, stream>>>(a);
-    else if (a.cap <= 2048) presorted_snapshot_kernel<128><<<grid, dim3(128), 0, stream>>>(a);
-    else if (a.cap <= 4096) presorted_snapshot_kernel<256><<<grid, dim3(256), 0, stream>>>(a);
-    else presorted_snapshot_kernel<512><<<grid, dim3(512), 0, stream>>>(a);
+    if (a.consistent) presorted_snapshot_kernel<512, true><<<grid, dim3(512), 0, stream>>>(a);
+    else if (a.cap <= 1024) presorted_snapshot_kernel<64, false><<<grid, dim3(64), 0, stream>>>(a);
+    else if (a.cap <= 2048) presorted_snapshot_kernel<128, false><<<grid, dim3(128), 0, stream>>>(a);
+    else if (a.cap <= 4096) presorted_snapshot_kernel<256, false><<<grid, dim3(256), 0, stream>>>(a);
+    else presorted_snapshot_kernel<512, false><<<grid, dim3(512), 0, stream>>>(a);
     return hipGetLastError();
 }
 
