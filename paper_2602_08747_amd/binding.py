@@ -147,15 +147,30 @@ def pard_workspace_bytes(plan: Plan, max_requests: int, max_snapshot_requests: i
     return b.value
 
 
+# A small call takes the device less time than the host: plain integers go to the C functions as they are (their argument
+# types convert them, None is a null pointer), and the current stream is asked for its handle without making an object of it.
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else ctypes.c_void_p(None)
+    return t.data_ptr() if t is not None and t.numel() > 0 else None
+
+
+_raw_stream = None
 
 
 def _stream_handle(stream):
-    if stream is None:
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+        torch.cuda.current_stream()                      # initialises the device context once
+        _raw_stream = (lambda: raw(device())) if raw is not None else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
+
+
+def _bytes(workspace) -> int:
+    return workspace.numel() * workspace.element_size()
 
 
 def pard_estimate_drop(plan: Plan, n: int, max_snapshot_requests: int, arrival, deadline, stage, snap_ptr, now,
@@ -164,7 +179,7 @@ def pard_estimate_drop(plan: Plan, n: int, max_snapshot_requests: int, arrival, 
     rc = load_library().pard_estimate_drop(
         plan.handle, int(n), int(max_snapshot_requests), _ptr(arrival), _ptr(deadline), _ptr(stage),
         _ptr(snap_ptr), _ptr(now), _ptr(est), _ptr(drop), _ptr(order), _ptr(seg_ptr),
-        _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream_handle(stream))
+        _ptr(workspace), _bytes(workspace), _stream_handle(stream))
     if check and rc != PARD_OK:
         raise PardError(rc, "pard_estimate_drop")
     return rc
@@ -190,7 +205,7 @@ def pard_estimate_drop_compact(plan: Plan, n: int, max_snapshot_requests: int, a
     rc = load_library().pard_estimate_drop_compact(
         plan.handle, int(n), int(max_snapshot_requests), _ptr(arrival), _ptr(deadline), _ptr(stage),
         _ptr(snap_ptr), _ptr(now), _ptr(est), _ptr(drop), _ptr(order), _ptr(seg_ptr), _ptr(surv_idx), _ptr(surv_ptr),
-        _ptr(workspace), int(workspace.numel() * workspace.element_size()),
+        _ptr(workspace), _bytes(workspace),
         ctypes.c_void_p(between_event) if between_event else ctypes.c_void_p(None), _stream_handle(stream))
     if check and rc != PARD_OK:
         raise PardError(rc, "pard_estimate_drop_compact")
@@ -203,7 +218,7 @@ def pard_estimate_drop_ranked(plan: Plan, n: int, max_snapshot_requests: int, ar
     rc = load_library().pard_estimate_drop_ranked(
         plan.handle, int(n), int(max_snapshot_requests), _ptr(arrival), _ptr(deadline), _ptr(stage),
         _ptr(snap_ptr), _ptr(now), _ptr(est), _ptr(drop), _ptr(order), _ptr(seg_ptr),
-        _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream_handle(stream))
+        _ptr(workspace), _bytes(workspace), _stream_handle(stream))
     if check and rc != PARD_OK:
         raise PardError(rc, "pard_estimate_drop_ranked")
     return rc
@@ -215,7 +230,7 @@ def pard_estimate_drop_sub(plan: Plan, n: int, max_snapshot_requests: int, arriv
     rc = load_library().pard_estimate_drop_sub(
         plan.handle, int(n), int(max_snapshot_requests), _ptr(arrival), _ptr(deadline), _ptr(stage), _ptr(snap_ptr),
         _ptr(now), _ptr(sub), _ptr(est), _ptr(drop), _ptr(order), _ptr(seg_ptr),
-        _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream_handle(stream))
+        _ptr(workspace), _bytes(workspace), _stream_handle(stream))
     if check and rc != PARD_OK:
         raise PardError(rc, "pard_estimate_drop_sub")
     return rc
@@ -227,7 +242,7 @@ def pard_estimate_drop_consistent(plan: Plan, n: int, max_snapshot_requests: int
     rc = load_library().pard_estimate_drop_consistent(
         plan.handle, int(n), int(max_snapshot_requests), _ptr(arrival), _ptr(deadline), _ptr(stage), _ptr(snap_ptr),
         _ptr(now), _ptr(sub), _ptr(est), _ptr(drop), _ptr(order), _ptr(seg_ptr),
-        _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream_handle(stream))
+        _ptr(workspace), _bytes(workspace), _stream_handle(stream))
     if check and rc != PARD_OK:
         raise PardError(rc, "pard_estimate_drop_consistent")
     return rc
@@ -306,7 +321,7 @@ def pard_compact(plan: Plan, n: int, max_snapshot_requests: int, order, seg_ptr,
     rc = load_library().pard_compact(
         plan.handle, int(n), int(max_snapshot_requests), _ptr(order), _ptr(seg_ptr), _ptr(drop), _ptr(surv_idx),
         _ptr(surv_ptr),
-        _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream_handle(stream))
+        _ptr(workspace), _bytes(workspace), _stream_handle(stream))
     if check and rc != PARD_OK:
         raise PardError(rc, "pard_compact")
     return rc
