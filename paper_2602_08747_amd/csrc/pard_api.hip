@@ -236,6 +236,7 @@ static int estimate_drop_impl(const pard_plan_t* plan, int64_t n, int64_t max_sn
         a.cap = (int32_t)max_snapshot_requests;
         a.consistent = consistent ? 1 : 0;
         a.n = n;
+        a.num_cus = plan->num_cus;
         e = launch_fused(a, s);
     } else {
         SortArgs a{};

@@ -211,6 +211,7 @@ struct FusedArgs {
     int32_t cap;                       // promised bound on a snapshot's size
     int32_t consistent;                // positions count only the kept requests ahead
     int64_t n;                         // total requests (bounds every index derived from snap_ptr)
+    int32_t num_cus;
 };
 hipError_t launch_fused(const FusedArgs& a, hipStream_t stream);
 // Snapshots whose requests already come in queue order (launch_fused tries this first when it applies).

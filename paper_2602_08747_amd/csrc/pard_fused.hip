@@ -44,10 +44,10 @@ namespace {
 constexpr int kFewStages = 8;
 constexpr int kSomeStages = 16;
 
-template <int CAP, int SCAP>
+template <int CAP, int SCAP, int T>
 struct SnapshotLds {
-    // 1.5 * CAP 16-bit counters, two per LDS word (2 * CAP at the smallest capacity: a thread scans an even number of words)
-    static constexpr int kCntWords = CAP == 256 ? CAP : CAP * 3 / 4;
+    // 1.5 * CAP 16-bit counters, two per LDS word (2 * CAP where a thread would not scan an even number of words)
+    static constexpr int kCntWords = CAP * 3 / 4 / T % 2 == 0 && CAP * 3 / 4 % T == 0 ? CAP * 3 / 4 : CAP;
     static constexpr int kAuxMin = SCAP * PARD_LAT_ENTRIES + 256;   // words: every stage's latency table + path entries
     static constexpr int kAuxWords = CAP / 2 > kAuxMin ? CAP / 2 : kAuxMin;
     __align__(16) uint32_t cnt32[kCntWords + 4];     // bucket counters, then bucket starts; later the queue order
@@ -71,13 +71,13 @@ constexpr int log2_of(int x) { return x <= 1 ? 0 : 1 + log2_of(x / 2); }
 // FULL: the snapshot holds exactly kCap requests and every array is 16-byte aligned at its
 // start, so no per-request bounds test is needed.
 template <int T, int CAP, int SCAP, bool FULL, bool CONSISTENT, bool AHEAD>
-__device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CAP, SCAP>& L, const int u, const int64_t lo,
+__device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CAP, SCAP, T>& L, const int u, const int64_t lo,
                                               const int m, const bool aligned, const int off) {
     constexpr int kCap = CAP;
     constexpr int kIdxBits = log2_of(CAP);                 // bits of a local index
-    constexpr int kCntWords = SnapshotLds<CAP, SCAP>::kCntWords;
+    constexpr int kCntWords = SnapshotLds<CAP, SCAP, T>::kCntWords;
     constexpr int kBuckets = 2 * kCntWords;                // 16-bit counters
-    constexpr int kAuxWords = SnapshotLds<CAP, SCAP>::kAuxWords;
+    constexpr int kAuxWords = SnapshotLds<CAP, SCAP, T>::kAuxWords;
     constexpr int G = kCap / (4 * T);       // groups of 4 consecutive requests per thread
     constexpr int CW = kCntWords / T;       // counter words scanned per thread
     // AHEAD, sequentially consistent under low budget first: in how many positions a request is in time is formed by all
@@ -685,7 +685,7 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
 template <int T, int CAP, int SCAP, bool CONSISTENT, bool AHEAD>
 __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = CAP;
-    __shared__ SnapshotLds<CAP, SCAP> L;
+    __shared__ SnapshotLds<CAP, SCAP, T> L;
     const int u = blockIdx.x;
     // (the mark and the snapshot's bounds are asked for together: one wait instead of two for a marked snapshot)
     const uint32_t marked = A.todo ? A.todo[u] : 1u;
@@ -744,11 +744,29 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     if (wave_path_covers(a)) { a.todo = nullptr; return launch_wave(a, stream); }      // a few dozen requests per snapshot: one wave each
     // Snapshots in queue order are finished by the kernel made for them; it marks the others in todo[],
     // and the general kernel below then works on the marked ones only (every other workgroup returns at once).
-    if (presorted_path_covers(a)) {
+    //
+    // Few snapshots, so few that workgroups of a thread per four requests (eight at the largest capacity) fit the chip
+    // at once (1024 threads to a compute unit at this kernel's registers): then a call takes as long as one snapshot's
+    // chain of phases, and every phase is shorter the more waves share it.  Estimate and compaction, 16 requests a thread
+    // and wide: one snapshot of 2000 23.9 and 14.5 us, of 4000 23.5 and 16.6; 200 of 2000 32.8 and 23.9; beyond the
+    // chip it turns round: 600 of 4000 38.4 and 47.9, 450 of 8000 45.5 and 51.5.  In a call of few requests altogether the
+    // kernel for queue order is a launch more than it saves, in order or not (one snapshot of a thousand, shuffled: 13.8 us
+    // behind it, 12.1 without; the largest capacity keeps it, 200 of 8000 in order 29.8 and 30.6).
+    const int wide_threads = a.cap <= 512 ? 128 : a.cap <= 1024 ? 256 : a.cap <= 2048 ? 512 : 1024;
+    const bool few = a.cap > 256 && (int64_t)a.plan.K * wide_threads <= 1024 * (int64_t)a.num_cus;
+    if (!(few && a.cap <= 4096 && a.n <= 8192) && presorted_path_covers(a)) {
         const hipError_t e = launch_presorted(a, stream);
         if (e != hipSuccess) return e;
     } else {
         a.todo = nullptr;
+    }
+    if (few) {
+        if (a.cap <= 512) launch_capacity<512, 128>(a, stream);
+        else if (a.cap <= 1024) launch_capacity<1024, 256>(a, stream);
+        else if (a.cap <= 2048) launch_capacity<2048, 512>(a, stream);
+        else if (a.cap <= 4096) launch_capacity<4096, 1024>(a, stream);
+        else launch_capacity<PARD_FUSED_SNAPSHOT_CAPACITY, 1024>(a, stream);
+        return hipGetLastError();
     }
     // the smallest workgroup whose capacity covers the promised snapshot size
     if (a.cap <= 256) launch_capacity<256, 64>(a, stream);
