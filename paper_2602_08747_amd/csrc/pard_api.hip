@@ -1,6 +1,7 @@
 // C-ABI of libpard (see include/pard.h): argument checks, plan upload, kernel launches.
 #include <cstring>
 #include <mutex>
+#include <vector>
 #include <new>
 
 #include "pard_device.hpp"
@@ -121,16 +122,25 @@ int pard_plan_create(pard_plan_t** out, const pard_plan_desc_t* desc) {
         delete p;
         return PARD_E_HIP;
     }
+    // The latency tables (most of the bytes) go up from where they are, the other tables in one copy: a copy of a few
+    // hundred bytes takes the host as long as one of a megabyte.
     char* base = static_cast<char*>(p->blob);
     int64_t off = 0;
+    std::vector<char> small;
+    try {
+        small.resize((size_t)(total - b_lat - b_drw));
+    } catch (...) {
+        (void)hipFree(p->blob);
+        delete p;
+        return PARD_E_BAD_SHAPE;
+    }
     auto put = [&](const void* src, size_t bytes, int64_t span) -> char* {
         char* dst = base + off;
+        if (bytes) memcpy(small.data() + off, src, bytes);
         off += span;
-        if (bytes && hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess) return nullptr;
         return dst;
     };
     char* d_recs = put(h.recs.data(), h.recs.size() * sizeof(StageRec), b_recs);
-    char* d_lat = put(h.lat.data(), h.lat.size() * 4, b_lat);
     char* d_dep = put(h.dag_entry_ptr.data(), h.dag_entry_ptr.size() * 4, b_dep);
     char* d_est = put(h.entry_stage.data(), h.entry_stage.size() * 4, b_est);
     char* d_een = put(h.entry_end.data(), h.entry_end.size() * 4, b_een);
@@ -138,8 +148,10 @@ int pard_plan_create(pard_plan_t** out, const pard_plan_desc_t* desc) {
     char* d_spi = put(h.split_in.data(), h.split_in.size() * 8, b_spl);
     char* d_spw = put(h.split_whole.data(), h.split_whole.size() * 8, b_spl);
     char* d_top = put(h.topo.data(), h.topo.size() * 4, b_top);
-    p->drawn = reinterpret_cast<uint32_t*>(base + off);
-    if (!d_top || !d_recs || !d_lat || !d_dep || !d_est || !d_een || !d_edg || !d_spi || !d_spw) {
+    char* d_lat = base + off;
+    p->drawn = reinterpret_cast<uint32_t*>(d_lat + b_lat);
+    if (hipMemcpy(base, small.data(), small.size(), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(d_lat, h.lat.data(), h.lat.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(p->blob);
         delete p;

@@ -889,9 +889,13 @@ hipError_t launch_queue_lengths(const PlanDev& plan, int64_t n, const int32_t* s
 hipError_t launch_sub_latency(const SubArgs& a, hipStream_t stream) {
     const PlanDev& P = a.plan;
     const int64_t segs = (int64_t)P.K * P.S;
-    const bool tails = a.variant == PARD_SUB_FULL && P.S <= kTStages && P.max_entries_per_dag <= kTEntries;
+    // Up to about two thousand path entries the workgroups of the path-by-path kernel fit the chip at once and a call takes
+    // as long as one of them, which finds its way to its samples sooner (157 snapshots of 3 stages: 29.7 us for the whole
+    // step path by path, 32.6 by sets; 489: 38.7 and 40.2; 800 of 8 stages, about 20,000 entries: 292 and 105).
+    const bool tails = a.variant == PARD_SUB_FULL && P.S <= kTStages && P.max_entries_per_dag <= kTEntries &&
+                       (P.shared ? (int64_t)P.K * P.max_entries_per_dag : P.total_entries) > 2048;
     // A workgroup per snapshot fills the chip from about a thousand snapshots on; below that the paths of a snapshot
-    // are dealt out to up to eight (70 snapshots: the whole planner step 21 us; 35 path by path).
+    // are dealt out to up to eight (800 snapshots of 8 stages: the whole planner step 105 us).
     const int32_t groups = P.K > 0 ? (P.K >= 1024 ? 1 : 1024 / P.K > 8 ? 8 : 1024 / P.K) : 1;
     if (a.variant != PARD_SUB_FULL) {                           // (the sampled variant's first kernel does it)
         int zb = (int)((segs + 255) / 256);

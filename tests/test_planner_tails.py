@@ -39,9 +39,10 @@ def gpu():
 CASES = [
     # K, S, requests, shared, latency scale (numerator, denominator), samples, lambda
     (1, 1, 50, 1, (1, 1), 100, (1, 2)),                     # nothing downstream
-    (1, 8, 300, 1, (1, 1), 2047, (1, 10)),                  # a few workgroups per snapshot; one below a block of samples
-    (3, 8, 200, 0, (1, 400), 2048, (1, 2048)),              # durations below 2^10: the integer form; the smallest total
-    (130, 5, 30, 0, (400, 1), 2049, (2048, 2049)),          # durations around 2^24; next to the largest total
+    (2, 8, 300, 1, (1, 1), 2047, (1, 10)),                  # few path entries: path by path
+    (300, 8, 40, 1, (1, 1), 2047, (1, 10)),                 # a few workgroups per snapshot; one below a block of samples
+    (250, 8, 30, 0, (1, 400), 2048, (1, 2048)),              # durations below 2^10: the integer form; the smallest total
+    (700, 5, 30, 0, (400, 1), 2049, (2048, 2049)),          # durations around 2^24; next to the largest total
     (1030, 4, 4, 0, (1, 1), 1, (1, 2)),                     # one workgroup per snapshot; one sample
     (1025, 6, 5, 1, (1, 30), 4097, (9, 10)),                # durations on both sides of 2^10
     (2, 9, 300, 0, (1, 1), 2049, (1, 10)),                  # nine stages: path by path
