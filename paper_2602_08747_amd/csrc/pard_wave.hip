@@ -3,9 +3,9 @@
 // The same result as the on-chip path for larger snapshots (paper Section 3.2 Eq.(1),(2),(4),
 // DAG maximum; Section 3.3 ordering), by other means: a workgroup sized for hundreds of
 // requests spends nearly all of its time on fixed costs (clearing and scanning bucket
-// counters, barriers) when a snapshot holds a few dozen.  Here a request is a 64-bit word
-// stage | order key | local index held in a register; a bitonic network over the wave's
-// lanes sorts the words, after which lane p holds the request of queue slot p:
+// counters, barriers) when a snapshot holds a few dozen.  Here a request is a word
+// stage | order key | local index held in a register (32 bits where they fit, else 64); a bitonic
+// network over the wave's lanes sorts the words, after which lane p holds the request of queue slot p:
 //   1. load deadline/stage (arrival for FCFS stages), form the word; deadlines go to LDS by
 //      local index
 //   2. sort (register exchanges across lanes; no LDS, no counters)
