@@ -189,11 +189,14 @@ __global__ __launch_bounds__(256) void sub_simple_kernel(SubArgs A, int64_t item
 constexpr int kTThreads = 512;
 constexpr int kTUnroll = 4;                             // samples of a thread in flight
 constexpr int kTBlock = kTThreads * kTUnroll;
+constexpr int kTRow = kWave * kTUnroll;                 // samples a wave takes at a time
 
-// Samples per stage in `drawn`, padded with arrivals at 0 so that sub_tails_kernel needs no bounds inside its loop.  An
-// arrival at 0 waits 0, the least there is, so the padding shifts the order statistic by its count and nothing else.
-__host__ __device__ __forceinline__ uint32_t tails_column(uint32_t M) { return (M + kTBlock - 1) / kTBlock * kTBlock; }
-static_assert(kMaxWaitSamples % kTBlock == 0, "the padded columns fit the plan's scratch");
+// Samples per stage in `drawn`, padded with arrivals at 0 to whole turns of a wave, so that sub_tails_kernel needs no bounds
+// inside its loop.  An arrival at 0 waits 0, the least there is, so the padding shifts the order statistic by its count and
+// nothing else.  (Not more of it than that: the padding of a mask piles onto one counter, and LDS adds to one word wait for
+// each other.)
+__host__ __device__ __forceinline__ uint32_t tails_column(uint32_t M) { return (M + kTRow - 1) / kTRow * kTRow; }
+static_assert(kMaxWaitSamples % kTRow == 0, "the padded columns fit the plan's scratch");
 
 // The arrival every (sample, stage) pair draws depends on neither the snapshot nor the path:
 // gather them once per call, stage-major, so that the per-path kernel below reads them with
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(kTThreads, 8) void sub_tails_kernel(SubArgs A, int3
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t u = (int32_t)(blockIdx.x / (unsigned)groups), group = (int32_t)(blockIdx.x % (unsigned)groups);
     const int S = P.S;                                          // <= kTStages
-    const uint32_t M = tails_column((uint32_t)A.num_samples);   // a multiple of kTBlock, see there
+    const uint32_t M = tails_column((uint32_t)A.num_samples);   // a multiple of kTRow, see there
     // The path entries come into LDS first (where the histograms are later), walked there: in memory the walk is a chain
     // of dependent loads.  The first wave meanwhile works out the stages.
     uint8_t* e_stage = reinterpret_cast<uint8_t*>(&L.hist[0][0]);
@@ -380,7 +383,7 @@ __global__ __launch_bounds__(kTThreads, 8) void sub_tails_kernel(SubArgs A, int3
                     if (!((some >> s) & 1u)) continue;
                     const uint32_t* col = A.drawn + s * M;
 #pragma unroll
-                    for (int x = 0; x < kTUnroll; ++x) w[s][x] = col[j0 + x * kTThreads];
+                    for (int x = 0; x < kTUnroll; ++x) w[s][x] = col[j0 + x * kWave];
                 }
 #pragma unroll
                 for (int s = 0; s < kTStages; ++s) {
@@ -434,8 +437,9 @@ __global__ __launch_bounds__(kTThreads, 8) void sub_tails_kernel(SubArgs A, int3
                     }
                 }
             };
-            if (round == 0) for (uint32_t j0 = tid; j0 < M; j0 += kTBlock) count_block(j0, std::false_type{});
-            else for (uint32_t j0 = tid; j0 < M; j0 += kTBlock) count_block(j0, std::true_type{});
+            const uint32_t own = (uint32_t)(wave * kTRow + lane);       // a wave's turn is a run of kTRow samples, M a multiple of it
+            if (round == 0) for (uint32_t j0 = own; j0 < M; j0 += kTBlock) count_block(j0, std::false_type{});
+            else for (uint32_t j0 = own; j0 < M; j0 += kTBlock) count_block(j0, std::true_type{});
             __syncthreads();
             if (wave < batch && L.hi[wave] > 0) {               // one wave per histogram, 16 counters a lane
                 const int hi = L.hi[wave];

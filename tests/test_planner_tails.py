@@ -46,6 +46,11 @@ CASES = [
     (1030, 4, 4, 0, (1, 1), 1, (1, 2)),                     # one workgroup per snapshot; one sample
     (1025, 6, 5, 1, (1, 30), 4097, (9, 10)),                # durations on both sides of 2^10
     (2, 9, 300, 0, (1, 1), 2049, (1, 10)),                  # nine stages: path by path
+    (1100, 3, 4, 1, (1, 1), 50, (1, 10)),                   # a wave takes 256 samples at a time: a part of one wave's,
+    (900, 4, 4, 0, (1, 30), 255, (1, 2)),                   # all but one,
+    (900, 4, 4, 0, (1, 1), 256, (255, 256)),                # all,
+    (1030, 4, 4, 0, (1, 30), 257, (1, 10)),                 # one into the next wave's,
+    (700, 5, 4, 0, (1, 1), 16384, (1, 10)),                 # the most samples there may be
 ]
 
 
