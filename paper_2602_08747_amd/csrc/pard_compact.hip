@@ -638,7 +638,7 @@ __global__ __launch_bounds__(THREADS, 4) void compact_local_kernel(CompactArgs A
 // request's place on) and a scan of the per-snapshot counts: one workgroup per snapshot moves its survivors and queue
 // offsets to their final place.  Everything a wave needs first comes from one round of independent loads, the
 // survivors from a second one; bound by the latency of those two, so a snapshot's survivors are spread over several
-// waves (one wave took three rounds for a few thousand: 3001 snapshots of up to 8001, 31 -> 20 us).  (Measured
+// waves where it may have more than one takes in a round (3001 snapshots of up to 8001: 31 us with one wave, 19 with eight).  (Measured
 // alternatives for 4096 snapshots: every wave adding up all earlier counts itself 22 us - all waves of the device read
 // the same few cache lines at once; 64 workgroups that add them up once and move 64 snapshots each 52 us - too few, too
 // long chains of dependent loads.)
@@ -701,9 +701,14 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
         uint32_t* snap_off = kept + ((K * 4 + 255) & ~(int64_t)255) / 4;
         if (a.staged) {                              // counted and staged by the estimate kernels: only the move is left
             snapshot_offsets_kernel<<<1, 1024, 0, stream>>>(a.kept, K, snap_off);
-            // 4096 snapshots of 4096, half kept: 64 threads 135 us for the call, 256: 128, 512: 122; of 3000: 138, 132, 135
-            if (a.max_snapshot >= 4096) move_staged_kernel<512><<<(unsigned)K, 512, 0, stream>>>(a, snap_off);
-            else move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
+            // The width follows the snapshots' mean size, not the promised bound, which may be loose: a wave moves 1024
+            // survivors in one round, and a workgroup of four or eight for a few dozen costs more than it saves.  The whole
+            // call with 64, 256 and 512 threads, most dropped / half kept: 50,000 snapshots of 60 under the bound 4096 580,
+            // 620 and 674 us; 10,000 of 1500 236, 239 and 247 / 262, 253 and 259; 4096 of 3000 76, 77 and 80 / 107, 104 and
+            // 103; 4096 of 4096 76, 76 and 80 / 118, 111 and 107; 2048 of 8192 74, 73 and 74 / 114, 108 and 104.
+            if (a.n > 4096 * K) move_staged_kernel<512><<<(unsigned)K, 512, 0, stream>>>(a, snap_off);
+            else if (a.n > 2048 * K) move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
+            else move_staged_kernel<kWave><<<(unsigned)K, kWave, 0, stream>>>(a, snap_off);
             return hipGetLastError();
         }
         // the smaller workgroup that covers the promised snapshot bound; up to 16 * THREADS snapshots every
