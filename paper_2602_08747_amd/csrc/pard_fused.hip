@@ -82,10 +82,8 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
     constexpr int CW = kCntWords / T;       // counter words scanned per thread
     // AHEAD, sequentially consistent under low budget first: in how many positions a request is in time is formed by all
     // threads side by side before a wave walks its queue; the walk, a chain of dependent steps, is then a prefix minimum per
-    // 64 requests instead of 64 estimates, a search and the minimum.  It costs instructions and saves waiting, so only the
-    // largest capacity has it, where a queue is longest: 3001 snapshots of up to 8001, three SLOs, 349 -> 291 us with the
-    // compaction, 4096 of 8192 shuffled 363 -> 352, in overload 332 -> 333, but 6000 of 3500 in overload 253 -> 287 and
-    // 10,000 of 1000 90 -> 105; and not under high budget first, whose walk needs one estimate per request (191 -> 234).
+    // 64 requests instead of 64 estimates, a search and the minimum.  It costs instructions and saves waiting, so it is for
+    // long queues (see launch_stages); not under high budget first, whose walk needs one estimate per request (191 -> 234).
     constexpr bool kAhead = AHEAD;
     static_assert(kCap == (1 << kIdxBits) && kCap <= PARD_FUSED_SNAPSHOT_CAPACITY, "capacity");
     static_assert(G >= 1 && CW >= 2 && CW % 2 == 0 && kCntWords % T == 0 && T % kWave == 0 && T / kWave <= 16, "shape");
@@ -716,10 +714,17 @@ __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     else snapshot_body<T, CAP, SCAP, false, CONSISTENT, AHEAD>(A, L, u, lo, m, aligned, off);
 }
 
+// Sequentially consistent: positions in time ahead of the walk (AHEAD) at the largest capacity, from a mean of more than 1024
+// requests per queue on.  With the compaction, the look of the kernel for queue order left out, 3000 snapshots of 8000 in
+// overload / half of them kept, plain walk and ahead: one queue each 580 / 613 and 371 / 373 us, three 309 / 336 and 274 / 287,
+// six 261 / 288 and 264 / 276, eight (1000 requests each) 240 / 269 and 255 / 273; six of 250 under the same promised bound
+// 415 / 417 and 444 / 422.  Smaller capacities: 6000 snapshots of 3500 in overload 253 and 287, 10,000 of 1000 90 and 105.
+constexpr int64_t kAheadQueue = 1024;
+
 template <int CAP, int T, int SCAP>
 void launch_stages(const FusedArgs& a, hipStream_t stream) {
     if constexpr (CAP == PARD_FUSED_SNAPSHOT_CAPACITY)
-        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF) {
+        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF && a.n > kAheadQueue * a.plan.K * a.plan.S) {
             fused_snapshot_kernel<T, CAP, SCAP, true, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
             return;
         }

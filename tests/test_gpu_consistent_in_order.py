@@ -16,11 +16,12 @@ def cost(pos, B, W, lat):
 
 
 def positions_in_time(budget, B, W, lat):
-    """The kernel's closed form, in float32 where it uses floats (short-queue waits: exact there, so integers here)."""
+    """The kernel's closed form, in float32 where it uses floats."""
     if budget < lat[0]:
         return 0
     b = min(budget, 2**32 - 1)
-    wait = lambda q: q * lat[B - 1] // W  # noqa: E731
+    aW, bW, one_over_w = int(lat[B - 1]) // W, int(lat[B - 1]) % W, np.float32(1.0) / np.float32(W)
+    wait = lambda q: q * aW + int((np.float32(q * bW) + np.float32(0.5)) * one_over_w)  # noqa: E731
     full, first = int(lat[B - 1]), int(wait(1))
     if b < full or b - full < first:
         if b < first:
@@ -91,6 +92,16 @@ CASES = {
 }
 
 
+CASES.update({   # more than 1024 requests per queue, so that the general kernel forms the positions ahead of the walk
+    "not-in-order-long": lambda: wl.random_workload(21, K=3, S=6, n_per_snapshot=8000, time_span=160_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000, 400_000), vary_sizes=False),
+    "not-in-order-many": lambda: wl.random_workload(22, K=257, S=3, n_per_snapshot=4100, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), dag_shared=1, vary_sizes=False),
+    "seven-stages-long": lambda: queued(23, 2, 7, 8192, vary_sizes=False),
+    "falling-tables-long": lambda: falling(queued(24, 2, 5, 6000, vary_sizes=False)),
+    "just-ahead": lambda: wl.random_workload(25, K=2, S=4, n_per_snapshot=4097, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
+    "just-not-ahead": lambda: wl.random_workload(25, K=2, S=4, n_per_snapshot=4096, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
+})
+
+
 def slow(w):
     return dataclasses.replace(w, workers=np.full_like(w.workers, 300))
 
@@ -109,3 +120,66 @@ def test_consistent_on_chip(oracle_mod, which):
     got = s.results()
     for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
         assert np.array_equal(got[k], ref[k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,S,per,bound,tried", [(3, 2, 4097, 8192, True), (3, 2, 4096, 8192, False), (40, 6, 300, 8192, False), (257, 1, 4097, 8192, True)])
+def test_in_order_kernel_by_mean_size(oracle_mod, K, S, per, bound, tried):
+    """The kernel for queue order is tried where snapshots fill more than half of its workgroup on average, whatever bound is
+    promised: it leaves a mark per snapshot behind the workspace's 256-byte header, and nothing else writes there."""
+    from paper_2602_08747_amd import binding
+    w = queued(per + K, K, S, per, vary_sizes=False, dag_shared=1)
+    ref = oracle_mod.run(w, threads=8, consistent=True)
+    s = binding.Session(w, max_snapshot_requests=bound)
+    s.workspace[64:64 + K] = -5
+    s.run(consistent=True)
+    got = s.results()
+    for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
+        assert np.array_equal(got[k], ref[k]), k
+    assert (s.workspace[64:64 + K].cpu().numpy() == (0 if tried else -5)).all()
+
+
+def boundary_snapshots(tables):
+    """One snapshot of one stage per (B, W, lat[B]): 8000 deadlines, each one microsecond before, at or behind the cost of a
+    position, most of them around a full batch; in every other snapshot of the first 5000 positions only, so that the queue
+    keeps up with the positions in time and one request more or less shows."""
+    rng = np.random.default_rng(len(tables))
+    K, per = len(tables), 8000
+    lat = np.zeros((K, 64), np.int64)
+    deadline = np.zeros((K, per), np.int64)
+    for u, (B, W, full) in enumerate(tables):
+        lat[u] = full - (np.maximum(B - 1 - np.arange(64), 0) * full) // 100          # rises up to the batch size, flat behind it
+        top = (8192, 5000)[u % 2]
+        pos = np.where(rng.random(per) < 0.7, rng.integers(0, top // B, per) * B + rng.integers(-1, 2, per), rng.integers(0, top, per))
+        deadline[u] = cost(np.clip(pos, 0, 8191), B, W, lat[u]) + rng.integers(-1, 2, per) - 2**31
+    assert deadline.max() < 2**31
+    deadline = np.sort(np.maximum(deadline, -2**31), axis=1)
+    n = K * per
+    rp, col = wl.csr_from_edges(1, [])
+    return wl.Workload(name=f"boundaries-{K}", K=K, S=1, dag_shared=0, dag_row_ptr=np.tile(rp, K), dag_col=np.tile(col, K).astype(np.int32),
+                       batch=np.array([t[0] for t in tables], np.int32), workers=np.array([t[1] for t in tables], np.int32),
+                       lat_us=np.ascontiguousarray(lat.reshape(-1), np.int32), order_mode=np.full(K, wl.MODE_LBF, np.int32),
+                       arrival=np.zeros(n, np.int32), deadline=np.ascontiguousarray(deadline.reshape(-1), np.int32), stage=np.zeros(n, np.int32),
+                       snap_ptr=(np.arange(K + 1) * per).astype(np.int32), now=np.full(K, -2**31, np.int32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shuffled", [False, True])
+@pytest.mark.parametrize("most", [(1 << 17) - 1, (1 << 18) - 1])
+def test_positions_in_time_at_every_step(oracle_mod, most, shuffled):
+    """Budgets on both sides of the costs, for the batch sizes and worker counts at the ends of the short form and whole
+    quotients of the wait just below 2^17 (as far as the kernel for queue order takes them) and 2^18 (the general one)."""
+    from paper_2602_08747_amd import binding
+    w = boundary_snapshots([(B, W, min(2**31 - 1, a * W + b)) for B in (1, 2, 3, 64) for W in (1, 3, 255, 256) for a in (7, 1000, most) for b in {0, W // 2, W - 1}])
+    if shuffled:
+        rng = np.random.default_rng(1)
+        w = dataclasses.replace(w, deadline=np.ascontiguousarray(rng.permuted(w.deadline.reshape(w.K, -1), axis=1).reshape(-1)))
+    ref = oracle_mod.run(w, threads=8, consistent=True)
+    assert 0.1 < ref["drop"].mean() < 0.9
+    s = binding.Session(w)
+    s.workspace[64:64 + w.K] = -5
+    s.run(consistent=True)
+    got = s.results()
+    for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
+        assert np.array_equal(got[k], ref[k]), k
+    assert (s.workspace[64:64 + w.K].cpu().numpy() == (-5 if most >= 1 << 17 else int(shuffled))).all()
