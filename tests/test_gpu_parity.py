@@ -241,6 +241,28 @@ def test_every_workgroup_capacity(gpu, oracle_mod, cap):
             assert np.array_equal(got[k], ref[k]), (cap, S, k)
 
 
+@pytest.mark.parametrize("K,cap", [(2049, 512), (1025, 1024), (513, 2048), (257, 4096), (257, 8192)])
+def test_every_workgroup_capacity_of_large_batches(gpu, oracle_mod, K, cap):
+    """The few snapshots above take wide workgroups; one snapshot more than those serve (1024 threads per compute unit, 256 of
+    them) takes sixteen requests a thread: full to the capacity and one short, in order and not, sequentially consistent, and
+    pipelines of 12 and of 17 stages."""
+    for per, permute in ((cap, True), (cap, False), (cap - 1, True)):
+        check(gpu, oracle_mod, wl.make_workload(5, n_snapshots=K, per_snapshot=per, permute=permute), max_snap=cap)
+    for S in (6, 12, 17):
+        w = wl.random_workload(700 + cap, K=K, S=S, n_per_snapshot=cap, dag_shared=1, vary_sizes=False, time_span=20 * cap,
+                               slo_choices=(3 * cap, 6 * cap))
+        w.lat_us[:] = np.maximum(1, w.lat_us // 20)
+        rng = np.random.default_rng(cap)
+        w = wl.with_snapshot_sizes(w, np.where(np.arange(K) % 3 == 2, rng.integers(0, cap + 1, K), cap))
+        s, ref = check(gpu, oracle_mod, w, max_snap=cap)
+        assert 0 < ref["drop"].mean() < 1
+        ref = oracle_mod.run(w, threads=8, consistent=True)
+        s.run(consistent=True)
+        got = s.results()
+        for k in KEYS:
+            assert np.array_equal(got[k], ref[k]), (cap, S, k)
+
+
 @pytest.mark.parametrize("per", [40, 700, 1500, 3000, 8000])
 def test_sixty_four_stages(gpu, oracle_mod, per):
     """The largest stage count: a chain of 64 stages plus a few shortcuts, every workgroup capacity, both paths."""

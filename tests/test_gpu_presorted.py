@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 
 INT32_MAX = 2**31 - 1
 KEYS = ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr")
+NO_MARK = -5                # what a snapshot's mark holds beforehand: no kernel writes it
 
 
 @pytest.fixture(scope="module")
@@ -27,6 +28,7 @@ def check(gpu, oracle_mod, w, max_snap=None, sub=None):
     print(f"case {w.name} n={w.n} K={w.K} S={w.S} max_snap={max_snap}", flush=True)
     ref = oracle_mod.run(w, threads=8, sub=sub)
     s = gpu.Session(w, max_snapshot_requests=max_snap)
+    s.workspace[64:64 + w.K] = NO_MARK
     s.run(sub=None if sub is None else torch.from_numpy(sub).to(s.dev))
     got = s.results()
     for k in KEYS:
@@ -49,7 +51,7 @@ def check(gpu, oracle_mod, w, max_snap=None, sub=None):
 
 def marks(s):
     """The workspace's word per snapshot behind its 256-byte header, as the in-order kernel left it:
-    0 = finished there, 1 = left to the general kernel."""
+    0 = finished there, 1 = left to the general kernel, NO_MARK = it did not run."""
     return s.workspace[64:64 + s.w.K].cpu().numpy()
 
 
@@ -58,7 +60,7 @@ def test_in_order_every_capacity(gpu, oracle_mod, cap):
     """Snapshots in arrival order that fill the workgroup's capacity exactly, fall short of it, and ragged mixes
     whose snapshots start at any offset of the request arrays."""
     for per in (cap, cap - 1, cap // 2 + 3, 300):
-        w = wl.make_workload(5, n_snapshots=6, per_snapshot=per)
+        w = wl.make_workload(5, n_snapshots=28, per_snapshot=per)          # more than 8192 requests in all
         s, ref = check(gpu, oracle_mod, w, max_snap=cap)
         assert (marks(s) == 0).all()                 # every snapshot was finished by the in-order kernel
         if per == 8192:
@@ -67,6 +69,14 @@ def test_in_order_every_capacity(gpu, oracle_mod, cap):
     sizes = np.random.default_rng(cap).integers(0, cap + 1, 60)
     check(gpu, oracle_mod, wl.with_snapshot_sizes(base, sizes), max_snap=cap)
     check(gpu, oracle_mod, wl.with_snapshot_sizes(base, np.minimum(sizes, 700)), max_snap=cap)
+
+
+@pytest.mark.parametrize("K,per,cap,runs", [(8, 1024, 1024, False), (9, 911, 1024, True), (2, 4096, 4096, False), (3, 2731, 4096, True),
+                                            (1, 5000, 8192, True)])
+def test_small_calls_leave_the_in_order_kernel_out(gpu, oracle_mod, K, per, cap, runs):
+    """Up to 8192 requests in all the general kernel takes them at once, except at the largest capacity."""
+    s, _ = check(gpu, oracle_mod, wl.make_workload(5, n_snapshots=K, per_snapshot=per), max_snap=cap)
+    assert (marks(s) == (0 if runs else NO_MARK)).all()
 
 
 def test_batch_mixing_ordered_and_shuffled_snapshots(gpu, oracle_mod):
@@ -126,11 +136,14 @@ def test_in_order_random_plans(gpu, oracle_mod, seed):
     """Random pipelines of up to six stages with the requests arranged by deadline: heavy ties, every batch size
     and worker count, latency tables that are not monotone, the downstream latency given from outside."""
     S = 1 + seed % 6
-    w = wl.in_deadline_order(wl.random_workload(4000 + seed, K=7, S=S, n_per_snapshot=1500, dag_shared=seed % 2,
+    w = wl.in_deadline_order(wl.random_workload(4000 + seed, K=14, S=S, n_per_snapshot=1500, dag_shared=seed % 2,
                                                 tie_heavy=(seed % 3 == 0), modes=(wl.MODE_LBF,), monotone=(seed % 2 == 0),
                                                 max_workers=300 if seed == 5 else 16))
+    if seed == 5:
+        w.workers[0] = 300                                 # more than the short form covers
+    assert w.n > 8192
     s, ref = check(gpu, oracle_mod, w)
-    assert (marks(s) == 0).all() or seed == 5          # seed 5 draws worker counts the short form does not cover
+    assert (marks(s) == (NO_MARK if seed == 5 else 0)).all()
     check(gpu, oracle_mod, w, max_snap=8192)
     sub = np.random.default_rng(seed).integers(0, 60_000, size=w.K * w.S).astype(np.int64)
     check(gpu, oracle_mod, w, sub=sub)
