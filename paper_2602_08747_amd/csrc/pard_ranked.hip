@@ -295,16 +295,26 @@ __global__ __launch_bounds__(T) void ranked_queues_kernel(RankedArgs A, int cap,
     const int range_bits = range ? 32 - __clz((int)range) : 0;
     const int shift = range_bits > bucket_bits ? range_bits - bucket_bits : 0;
     auto bucket = [&](int mode, int32_t d) { return (mode == PARD_ORDER_HBF ? (uint32_t)high - (uint32_t)d : (uint32_t)d - (uint32_t)low) >> shift; };
-    // where every bucket begins: the slot before and the slot itself say which buckets begin at it
+    // where every bucket begins: the slot before and the slot itself say which buckets begin at it, and those behind the
+    // last slot's begin at the queue's end.  A run of more than a few (a far deadline leaves most buckets empty) is written
+    // by the whole wave.
     each_chunk([&](int k, int begin, int len, int pos) {
         const int mode = P.uniform_mode >= 0 ? P.uniform_mode : __builtin_amdgcn_readfirstlane(recs[k].mode) & 0xFF;
-        if (mode == PARD_ORDER_FCFS || pos >= len) return;
+        if (mode == PARD_ORDER_FCFS) return;
         uint16_t* row = table + k * (buckets + 1);
-        const int mine = (int)bucket(mode, dls[begin + pos]);
-        int b = __builtin_amdgcn_update_dpp(0, mine, 0x138, 0xF, 0xF, false) + 1;       // wave_shr:1, the slot before
-        if ((pos & 63) == 0) b = pos > 0 ? (int)bucket(mode, dls[begin + pos - 1]) + 1 : 0;
-        for (; b <= mine; ++b) row[b] = (uint16_t)pos;
-        if (pos == len - 1) for (int b = mine + 1; b <= buckets; ++b) row[b] = (uint16_t)len;
+        const int last = pos < len ? (int)bucket(mode, dls[begin + pos]) : pos == len ? buckets : -1;
+        int first = __builtin_amdgcn_update_dpp(0, last, 0x138, 0xF, 0xF, false) + 1;       // wave_shr:1, the slot before
+        if (lane == 0) first = pos > 0 ? (int)bucket(mode, dls[begin + pos - 1]) + 1 : 0;
+        auto fill = [&](int from, int to, int slot) { for (int b = from + lane; b <= to; b += kWave) row[b] = (uint16_t)slot; };
+        constexpr int kRun = 6;
+        unsigned long long runs = __ballot(last - first >= kRun);
+        if (last - first < kRun) for (int b = first; b <= last; ++b) row[b] = (uint16_t)pos;
+        while (runs) {
+            const int l = __builtin_ctzll(runs);
+            runs &= runs - 1ull;
+            fill(from_lane(first, l), from_lane(last, l), from_lane(pos, l));
+        }
+        if (from_lane(pos, kWave - 1) == len - 1) fill(from_lane(last, kWave - 1) + 1, buckets, len);
     });
     __syncthreads();
     each_chunk([&](int k, int begin, int len, int pos) {
@@ -363,13 +373,19 @@ __global__ __launch_bounds__(T) void ranked_queues_kernel(RankedArgs A, int cap,
 }  // namespace
 
 hipError_t launch_ranked(const RankedArgs& a, hipStream_t stream) {
+    if (a.plan.S == 1) return hipSuccess;              // no later queue: the plain call's estimates are the ranked ones
     if (a.n <= 0) return hipSuccess;
     // the largest workgroup whose per-thread rows and the snapshot's deadlines fit 64 KB of LDS
     const int64_t cap = a.max_snapshot < 1 ? 1 : a.max_snapshot;
     auto lds_bytes = [&](int threads) { return (size_t)a.plan.S * threads * sizeof(unsigned long long) + (size_t)((cap + 1) & ~(int64_t)1) * 4; };
     if (a.max_snapshot <= PARD_FUSED_SNAPSHOT_CAPACITY && a.plan.S <= kTopoStages) {
         // About one slot of a queue to a bucket, at most 1024 (512 from 9 stages on: the tables then take 16 KB).  Threads
-        // as for the general on-chip kernel: 16 slots each, fewer for the smallest snapshots.
+        // as for the general on-chip kernel: 16 slots each, fewer for the smallest snapshots.  Eight stages or 16, with and
+        // without the short cost form: unrolled for more places than there are stages the kernel needs more registers and
+        // skips the rest one by one (1000 snapshots of 4000, three stages with 300 workers: 99 us with 16 places, 87 with 8;
+        // a search of the whole queue and a walk of the paths 96).  Where it gains least that search is still as fast or a
+        // little faster: two stages with 300 workers, 5000 snapshots of 700 89 and 88 us, 30,000 of 200 155 and 151; 5000 of
+        // 700 in two queues with one deadline far from all others 376 and 366.
         const bool few = a.plan.S <= 8;
         int bits = 4;
         while (bits < (few ? 10 : 9) && ((int64_t)8 << bits) < cap) ++bits;
@@ -381,6 +397,10 @@ hipError_t launch_ranked(const RankedArgs& a, hipStream_t stream) {
             if (cap > 2048) launch(ranked_queues_kernel<8, 512, true>, 512);
             else if (cap > 512) launch(ranked_queues_kernel<8, 256, true>, 256);
             else launch(ranked_queues_kernel<8, 128, true>, 128);
+        } else if (few) {
+            if (cap > 2048) launch(ranked_queues_kernel<8, 512, false>, 512);
+            else if (cap > 512) launch(ranked_queues_kernel<8, 256, false>, 256);
+            else launch(ranked_queues_kernel<8, 128, false>, 128);
         } else if (a.plan.presorted_ok) {
             if (cap > 2048) launch(ranked_queues_kernel<kTopoStages, 512, true>, 512);
             else if (cap > 512) launch(ranked_queues_kernel<kTopoStages, 256, true>, 256);

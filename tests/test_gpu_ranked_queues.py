@@ -36,7 +36,27 @@ CASES = {
     if case(8, 4, 7, 700).dag_shared == 0 else dataclasses.replace(case(8, 4, 7, 700), workers=np.full(7, 300, np.int32)),
     "wide": lambda: wide(case(9, 3, 6, 900, modes=(wl.MODE_LBF, wl.MODE_HBF)), 9),
     "one-outlier": lambda: outlier(case(10, 2, 4, 3000, modes=(wl.MODE_LBF,))),
+    "one-outlier-hbf": lambda: outlier(case(11, 3, 3, 700, modes=(wl.MODE_HBF,))),
+    "whole-rows": lambda: alternating(case(12, 3, 2, 256, modes=(wl.MODE_LBF,), vary_sizes=False)),
+    "whole-rows-outlier": lambda: outlier(alternating(case(13, 3, 2, 2048, modes=(wl.MODE_LBF,), vary_sizes=False))),
+    "one-stage": lambda: case(14, 5, 1, 700),
+    "one-stage-wave": lambda: case(15, 50, 1, 40),
+    "one-stage-large": lambda: case(16, 2, 1, 9000, vary_sizes=False),
+    "two-slow-stages-200": lambda: slow(case(17, 9, 2, 100)),
+    "two-slow-stages-700": lambda: slow(case(18, 4, 2, 700, vary_sizes=False)),
+    "eight-slow-stages-4000": lambda: slow(case(19, 2, 8, 4000, vary_sizes=False)),
+    "nine-slow-stages": lambda: slow(case(20, 2, 9, 600, vary_sizes=False)),
 }
+
+
+def slow(w):
+    """More workers than the short cost form covers."""
+    return dataclasses.replace(w, workers=np.full_like(w.workers, 300))
+
+
+def alternating(w):
+    """Queues of whole rows of 64 slots."""
+    return dataclasses.replace(w, stage=(np.arange(w.n) % w.S).astype(np.int32))
 
 
 def outlier(w):
