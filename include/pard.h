@@ -31,11 +31,9 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  The two
  *     hot calls only enqueue kernels: they do not allocate, free or synchronise.
  *   - A plan changes only through pard_plan_set_modes.  It may be used from several
- *     streams at once, provided each concurrent call has its own workspace.  Two
- *     exceptions: the sampled variant of pard_sub_latency, which stages its draws in
- *     scratch memory the plan owns (see there), and pard_compact where it compacts the
- *     queues as one stream (see there): its workgroups wait for each other and need the
- *     device's compute units to themselves.
+ *     streams at once, provided each concurrent call has its own workspace.  One
+ *     exception: the sampled variant of pard_sub_latency, which stages its draws in
+ *     scratch memory the plan owns (see there).
  */
 #ifndef PARD_H_
 #define PARD_H_
@@ -201,11 +199,12 @@ int pard_estimate_drop_static(const pard_plan_t* plan, int64_t n, int64_t max_sn
  *   max_snapshot_requests  promised upper bound on the requests of one snapshot, as for
  *                          pard_estimate_drop: from 2049 to PARD_FUSED_SNAPSHOT_CAPACITY every
  *                          snapshot is compacted by one workgroup, below and above that the
- *                          queues are compacted as one stream (where the bound plays no
- *                          further role).  A snapshot larger than the workgroup chosen for
- *                          such a bound can hold (the bound rounded up to 4096 or 8192)
- *                          raises bit 0 of the status word; the outputs are then unspecified
- *                          (never out of bounds)
+ *                          queues are compacted as one stream, or all by one workgroup when
+ *                          they are few (where the bound plays no further role).  A
+ *                          snapshot larger than the workgroup chosen for a bound from 2049
+ *                          on can hold (the bound rounded up to 4096 or 8192) raises bit 0
+ *                          of the status word; the outputs are then unspecified (never out
+ *                          of bounds)
  *                          Neither form makes a workgroup wait for another one: like every call
  *                          here it may share the device with other work on other streams.
  *   d_order, d_seg_ptr     as written by pard_estimate_drop

@@ -394,6 +394,7 @@ static int sub_latency_impl(const pard_plan_t* plan, const int32_t* d_qlen, cons
     a.qlen = d_qlen;
     a.qdelay = d_qdelay;
     a.variant = variant;
+    a.num_cus = plan->num_cus;
     a.sub = reinterpret_cast<unsigned long long*>(d_sub);
     if (variant == PARD_SUB_FULL) {
         if (lambda_den <= 0 || lambda_num < 0 || lambda_num > lambda_den) return PARD_E_BAD_SHAPE;

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kTThreads, 8) void sub_tails_kernel(SubArgs A, int3
     }
 }
 
-// More than 8 stages: one workgroup per (snapshot, path entry).
+// More than 8 stages, few path entries, or a DAG of more than kTEntries: one workgroup per (snapshot, path entry).
 constexpr int kWThreads = 512;
 constexpr int kWWaves = kWThreads / kWave;
 constexpr int kWUnroll = 8;                            // samples a thread works on at once
@@ -893,14 +893,17 @@ hipError_t launch_queue_lengths(const PlanDev& plan, int64_t n, const int32_t* s
 hipError_t launch_sub_latency(const SubArgs& a, hipStream_t stream) {
     const PlanDev& P = a.plan;
     const int64_t segs = (int64_t)P.K * P.S;
-    // Up to about two thousand path entries the workgroups of the path-by-path kernel fit the chip at once and a call takes
-    // as long as one of them, which finds its way to its samples sooner (157 snapshots of 3 stages: 29.7 us for the whole
-    // step path by path, 32.6 by sets; 489: 38.7 and 40.2; 800 of 8 stages, about 20,000 entries: 292 and 105).
+    // By sets of stages from more than eight path entries per compute unit on (2048 on this device): below that the workgroups
+    // of the path-by-path kernel fit the chip at once or nearly, and a call takes as long as one of them, which finds its way
+    // to its samples sooner.  The crossing lies between 1200 and 2000 entries for every pipeline tried; the whole planner step
+    // with 10,000 samples, path by path and by sets, at about 1500, 2000, 4000 and 8000 entries: chain of 3 stages 48 / 52, 52 /
+    // 50, 74 / 71, 117 / 106 us; DAGs of 5 stages 36 / 38, 56 / 57, 80 / 59, 128 / 69; of 8 40 / 41, 46 / 41, 73 / 52, 141 / 84.
     const bool tails = a.variant == PARD_SUB_FULL && P.S <= kTStages && P.max_entries_per_dag <= kTEntries &&
-                       (P.shared ? (int64_t)P.K * P.max_entries_per_dag : P.total_entries) > 2048;
-    // A workgroup per snapshot fills the chip from about a thousand snapshots on; below that the paths of a snapshot
-    // are dealt out to up to eight (800 snapshots of 8 stages: the whole planner step 105 us).
-    const int32_t groups = P.K > 0 ? (P.K >= 1024 ? 1 : 1024 / P.K > 8 ? 8 : 1024 / P.K) : 1;
+                       (P.shared ? (int64_t)P.K * P.max_entries_per_dag : P.total_entries) > 8 * (int64_t)a.num_cus;
+    // A workgroup per snapshot fills the chip from four per compute unit on (a thousand snapshots); below that the paths of a
+    // snapshot are dealt out to up to eight (800 snapshots of 8 stages: the whole planner step 105 us).
+    const int32_t fill = 4 * a.num_cus;
+    const int32_t groups = P.K > 0 ? (P.K >= fill ? 1 : fill / P.K > 8 ? 8 : fill / P.K) : 1;
     if (a.variant != PARD_SUB_FULL) {                           // (the sampled variant's first kernel does it)
         int zb = (int)((segs + 255) / 256);
         if (zb > 1024) zb = 1024;
