@@ -753,17 +753,17 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // Few snapshots take wide workgroups, a thread per four requests (eight at the largest capacity), up to 1024 threads per
     // compute unit: a call then takes as long as one snapshot's chain of phases, and every phase is shorter the more waves
     // share it.  Two such shares would fit a compute unit by the registers (58 to 63 up to 4096 requests; 84 to 94 at 8192
-    // leave room for one; the narrow shapes take up to 128), but where a workgroup is 1024 threads it turns right behind the first: estimate and
-    // compaction, shuffled, narrow and wide, 256 snapshots of 4000 32.3 and 25.2 us, 320 35.0 and 36.4, 600 41.0 and 50.6;
-    // 256 of 8000 38.3 and 34.7, 300 45.0 and 50.7.  The smaller shapes gain for longer and less evenly: 768 of 2000 (1.5
-    // shares) 38.9 and 30.8, 1536 45.5 and 44.7; 1500 of 1000 35.0 and 32.1, 2048 36.4 and 38.5, 3000 49.9 and 45.8; 3000 of
-    // 500 36.2 and 31.2, 4096 37.3 and 38.0.
+    // leave room for one; the narrow shapes take up to 128), but where a workgroup is 1024 threads it turns right behind the
+    // first: estimate and compaction, shuffled, narrow and wide, 256 snapshots of 4000 32.3 and 25.2 us, 320 35.0 and 36.4,
+    // 600 41.0 and 50.6; 256 of 8000 38.3 and 34.7, 300 45.0 and 50.7.  The smaller shapes gain for longer and less evenly:
+    // 768 of 2000 (1.5 shares) 38.9 and 30.8, 1536 45.5 and 44.7; 1500 of 1000 35.0 and 32.1, 2048 36.4 and 38.5, 3000 49.9
+    // and 45.8; 3000 of 500 36.2 and 31.2, 4096 37.3 and 38.0.
     //
     // The kernel for queue order is left out of small calls, where it is a launch more than it saves, in order or not (one
     // snapshot of a thousand 16.9 and 12.6 us in order, 15.9 and 14.0 shuffled; eight 19.4 and 15.1, 17.7 and 15.5; two of
-    // 4000 19.5 and 18.2, 20.5 and 18.3).  The limit says what is taken for small, it is not a
-    // crossing: the difference is the same at 256 snapshots of a thousand (23.1 and 19.1).  The largest capacity keeps the
-    // kernel (200 of 8000 in order 29.8 with it, 30.6 without).
+    // 4000 19.5 and 18.2, 20.5 and 18.3).  The limit says what is taken for small, it is not a crossing: the difference is
+    // the same at 256 snapshots of a thousand (23.1 and 19.1).  The largest capacity keeps the kernel (200 of 8000 in order
+    // 29.8 with it, 30.6 without).
     const int wide_threads = a.cap <= 512 ? 128 : a.cap <= 1024 ? 256 : a.cap <= 2048 ? 512 : 1024;
     const bool few = a.cap > 256 && (int64_t)a.plan.K * wide_threads <= 1024 * (int64_t)a.num_cus;
     if (!(few && a.cap <= 4096 && a.n <= 8192) && presorted_path_covers(a)) {
