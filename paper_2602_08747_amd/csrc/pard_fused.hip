@@ -715,16 +715,19 @@ __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
 }
 
 // Sequentially consistent: positions in time ahead of the walk (AHEAD) at the largest capacity, from a mean of more than 1024
-// requests per queue on.  With the compaction, the look of the kernel for queue order left out, 3000 snapshots of 8000 in
-// overload / half of them kept, plain walk and ahead: one queue each 580 / 613 and 371 / 373 us, three 309 / 336 and 274 / 287,
-// six 261 / 288 and 264 / 276, eight (1000 requests each) 240 / 269 and 255 / 273; six of 250 under the same promised bound
-// 415 / 417 and 444 / 422.  Smaller capacities: 6000 snapshots of 3500 in overload 253 and 287, 10,000 of 1000 90 and 105.
-constexpr int64_t kAheadQueue = 1024;
+// requests per queue on; 512 with the wide workgroups of few snapshots, where a call takes as long as one chain.  With the
+// compaction, the look of the kernel for queue order left out, 3000 snapshots of 8000 in overload / half of them kept, plain
+// walk and ahead: one queue each 580 / 613 and 371 / 373 us, three 309 / 336 and 274 / 287, six 261 / 288 and 264 / 276, eight
+// (1000 requests each) 240 / 269 and 255 / 273; six of 250 under the same promised bound 415 / 417 and 444 / 422.  Smaller
+// capacities: 6000 snapshots of 3500 in overload 253 and 287, 10,000 of 1000 90 and 105.  Wide, 100 snapshots: 1000 a queue
+// 36.3 / 37.5 and 35.1 / 35.2, 667 33.9 / 35.1 and 35.0 / 34.5, 417 31.2 / 31.5 and 33.3 / 31.9, 100 21.6 / 21.6 and 24.1 / 22.9.
+constexpr int64_t kAheadQueue = 1024, kAheadQueueWide = 512;
 
 template <int CAP, int T, int SCAP>
 void launch_stages(const FusedArgs& a, hipStream_t stream) {
     if constexpr (CAP == PARD_FUSED_SNAPSHOT_CAPACITY)
-        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF && a.n > kAheadQueue * a.plan.K * a.plan.S) {
+        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF &&
+            a.n > (T > 512 ? kAheadQueueWide : kAheadQueue) * a.plan.K * a.plan.S) {
             fused_snapshot_kernel<T, CAP, SCAP, true, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
             return;
         }
@@ -763,10 +766,13 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // snapshot of a thousand 16.9 and 12.6 us in order, 15.9 and 14.0 shuffled; eight 19.4 and 15.1, 17.7 and 15.5; two of
     // 4000 19.5 and 18.2, 20.5 and 18.3).  The limit says what is taken for small, it is not a crossing: the difference is
     // the same at 256 snapshots of a thousand (23.1 and 19.1).  The largest capacity keeps the kernel (200 of 8000 in order
-    // 29.8 with it, 30.6 without).
+    // 29.8 with it, 30.6 without), but not under sequentially consistent dropping, where the wide workgroups are ahead of it
+    // also in order: 100 snapshots of 5000, six stages, 36.0 and 32.0 us in order, 34.4 and 32.0 shuffled, of 8000 36.7 and
+    // 34.4, 38.1 and 35.0.
     const int wide_threads = a.cap <= 512 ? 128 : a.cap <= 1024 ? 256 : a.cap <= 2048 ? 512 : 1024;
     const bool few = a.cap > 256 && (int64_t)a.plan.K * wide_threads <= 1024 * (int64_t)a.num_cus;
-    if (!(few && a.cap <= 4096 && a.n <= 8192) && presorted_path_covers(a)) {
+    const bool alone = few && (a.consistent || (a.cap <= 4096 && a.n <= 8192));
+    if (!alone && presorted_path_covers(a)) {
         const hipError_t e = launch_presorted(a, stream);
         if (e != hipSuccess) return e;
     } else {

@@ -92,12 +92,14 @@ CASES = {
 }
 
 
-CASES.update({   # more than 1024 requests per queue, so that the general kernel forms the positions ahead of the walk
+CASES.update({   # more than 1024 requests per queue (512 of few snapshots), so that the general kernel forms the positions ahead of the walk
     "not-in-order-long": lambda: wl.random_workload(21, K=3, S=6, n_per_snapshot=8000, time_span=160_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000, 400_000), vary_sizes=False),
     "not-in-order-many": lambda: wl.random_workload(22, K=257, S=3, n_per_snapshot=4100, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), dag_shared=1, vary_sizes=False),
     "seven-stages-long": lambda: queued(23, 2, 7, 8192, vary_sizes=False),
     "falling-tables-long": lambda: falling(queued(24, 2, 5, 6000, vary_sizes=False)),
     "just-ahead": lambda: wl.random_workload(25, K=2, S=4, n_per_snapshot=4097, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
+    "just-ahead-wide": lambda: wl.random_workload(26, K=2, S=8, n_per_snapshot=4097, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
+    "just-not-ahead-wide": lambda: wl.random_workload(26, K=2, S=8, n_per_snapshot=4096, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
     "just-not-ahead": lambda: wl.random_workload(25, K=2, S=4, n_per_snapshot=4096, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
 })
 
@@ -106,14 +108,25 @@ def slow(w):
     return dataclasses.replace(w, workers=np.full_like(w.workers, 300))
 
 
+def repeated(w, least):
+    """The same snapshots over and over, at least so many."""
+    times = -(-least // w.K)
+    tile = lambda a: np.tile(a, times)  # noqa: E731
+    plan = {} if w.dag_shared else {k: tile(getattr(w, k)) for k in ("dag_row_ptr", "dag_col", "batch", "workers", "lat_us", "order_mode")}
+    sizes = np.diff(w.snap_ptr)
+    return dataclasses.replace(w, K=w.K * times, arrival=tile(w.arrival), deadline=tile(w.deadline), stage=tile(w.stage), now=tile(w.now),
+                               snap_ptr=np.concatenate([[0], np.cumsum(tile(sizes))]).astype(np.int32), **plan)
+
+
 @pytest.mark.gpu
+@pytest.mark.parametrize("least", [1, 257])               # wide workgroups; the kernel for queue order, and one workgroup's usual width
 @pytest.mark.parametrize("which", list(CASES))
-def test_consistent_on_chip(oracle_mod, which):
+def test_consistent_on_chip(oracle_mod, which, least):
     import torch
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a GPU and the built libpard.so")
     from paper_2602_08747_amd import binding
-    w = CASES[which]()
+    w = repeated(CASES[which](), least)
     ref = oracle_mod.run(w, threads=8, consistent=True)
     s = binding.Session(w)
     s.run(consistent=True)
@@ -123,10 +136,12 @@ def test_consistent_on_chip(oracle_mod, which):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("K,S,per,bound,tried", [(3, 2, 4097, 8192, True), (3, 2, 4096, 8192, False), (40, 6, 300, 8192, False), (257, 1, 4097, 8192, True)])
+@pytest.mark.parametrize("K,S,per,bound,tried", [(257, 2, 4097, 8192, True), (257, 2, 4096, 8192, False), (300, 6, 300, 8192, False),
+                                                     (256, 2, 4097, 8192, False), (3, 2, 8000, 8192, False)])
 def test_in_order_kernel_by_mean_size(oracle_mod, K, S, per, bound, tried):
     """The kernel for queue order is tried where snapshots fill more than half of its workgroup on average, whatever bound is
-    promised: it leaves a mark per snapshot behind the workspace's 256-byte header, and nothing else writes there."""
+    promised, and are too many for the wide workgroups: it leaves a mark per snapshot behind the workspace's 256-byte header, and
+    nothing else writes there."""
     from paper_2602_08747_amd import binding
     w = queued(per + K, K, S, per, vary_sizes=False, dag_shared=1)
     ref = oracle_mod.run(w, threads=8, consistent=True)
@@ -165,12 +180,14 @@ def boundary_snapshots(tables):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("shuffled", [False, True])
+@pytest.mark.parametrize("least", [1, 257])
 @pytest.mark.parametrize("most", [(1 << 17) - 1, (1 << 18) - 1])
-def test_positions_in_time_at_every_step(oracle_mod, most, shuffled):
+def test_positions_in_time_at_every_step(oracle_mod, most, least, shuffled):
     """Budgets on both sides of the costs, for the batch sizes and worker counts at the ends of the short form and whole
     quotients of the wait just below 2^17 (as far as the kernel for queue order takes them) and 2^18 (the general one)."""
     from paper_2602_08747_amd import binding
     w = boundary_snapshots([(B, W, min(2**31 - 1, a * W + b)) for B in (1, 2, 3, 64) for W in (1, 3, 255, 256) for a in (7, 1000, most) for b in {0, W // 2, W - 1}])
+    w = repeated(w, least)
     if shuffled:
         rng = np.random.default_rng(1)
         w = dataclasses.replace(w, deadline=np.ascontiguousarray(rng.permuted(w.deadline.reshape(w.K, -1), axis=1).reshape(-1)))
@@ -182,4 +199,4 @@ def test_positions_in_time_at_every_step(oracle_mod, most, shuffled):
     got = s.results()
     for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
         assert np.array_equal(got[k], ref[k]), k
-    assert (s.workspace[64:64 + w.K].cpu().numpy() == (-5 if most >= 1 << 17 else int(shuffled))).all()
+    assert (s.workspace[64:64 + w.K].cpu().numpy() == (-5 if most >= 1 << 17 or least == 1 else int(shuffled))).all()
