@@ -74,7 +74,8 @@ __global__ __launch_bounds__(kQThreads) void queue_lengths_kernel(int32_t K, int
         if (local) atomicAdd(&bins[((u - u_lo) * S + s) * copies + (tid & (copies - 1))], 1u);
         else atomicAdd(&qlen[(int64_t)u * S + s], 1);
     };
-    if (vec && base + kQChunk <= n) {                  // a whole chunk: 16-byte loads, all of them issued first
+    if (vec && local && base + kQChunk <= n) {         // a whole chunk: 16-byte loads, all of them issued first (counting in memory,
+                                                       // neighbouring lanes better count neighbouring requests)
         int4 v[kQChunk / (4 * kQThreads)];
 #pragma unroll
         for (int i = 0; i < kQChunk / (4 * kQThreads); ++i) v[i] = reinterpret_cast<const int4*>(stage + base)[i * kQThreads + tid];
@@ -904,12 +905,13 @@ hipError_t launch_sub_latency(const SubArgs& a, hipStream_t stream) {
     // snapshot are dealt out to up to eight (800 snapshots of 8 stages: the whole planner step 105 us).
     const int32_t fill = 4 * a.num_cus;
     const int32_t groups = P.K > 0 ? (P.K >= fill ? 1 : fill / P.K > 8 ? 8 : fill / P.K) : 1;
-    if (a.variant != PARD_SUB_FULL) {                           // (the sampled variant's first kernel does it)
+    const bool nothing_behind = a.variant == PARD_SUB_BACK || P.S == 1;
+    if (a.variant != PARD_SUB_FULL || nothing_behind) {         // (the sampled variant's first kernel does it)
         int zb = (int)((segs + 255) / 256);
         if (zb > 1024) zb = 1024;
         fill_zero_kernel<<<zb, 256, 0, stream>>>(a.sub, segs);
     }
-    if (a.variant == PARD_SUB_BACK) return hipGetLastError();
+    if (nothing_behind) return hipGetLastError();
     const int64_t items = P.shared ? (int64_t)P.K * P.max_entries_per_dag : P.total_entries;
     if (items <= 0) return hipGetLastError();       // no snapshot
     if (a.variant != PARD_SUB_FULL) {

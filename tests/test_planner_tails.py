@@ -39,6 +39,7 @@ def gpu():
 CASES = [
     # K, S, requests, shared, latency scale (numerator, denominator), samples, lambda
     (1, 1, 50, 1, (1, 1), 100, (1, 2)),                     # nothing downstream
+    (3000, 1, 4, 1, (1, 1), 100, (1, 2)),                   # nor in many snapshots
     (2, 8, 300, 1, (1, 1), 2047, (1, 10)),                  # few path entries: path by path
     (300, 8, 40, 1, (1, 1), 2047, (1, 10)),                 # a few workgroups per snapshot; one below a block of samples
     (250, 8, 30, 0, (1, 400), 2048, (1, 2048)),              # durations below 2^10: the integer form; the smallest total
@@ -80,7 +81,7 @@ def test_sampled_quantile_by_stage_set(gpu, oracle_mod, K, S, requests, shared, 
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("K,n,offset", [(1, 16384, 0), (1, 16385, 0), (4096, 9000, 1), (4097, 9000, 0), (3, 40961, 1), (5, 16, 3), (2, 0, 0)])
+@pytest.mark.parametrize("K,n,offset", [(1, 16384, 0), (1, 16385, 0), (4096, 9000, 1), (4097, 9000, 0), (3, 40961, 1), (5, 16, 3), (2, 0, 0), (16385, 16500, 0)])
 def test_queue_length_dispatch(gpu, K, n, offset):
     """Both ways of counting at the edges of their rule; offset: the stage array off a 16-byte boundary."""
     import torch
