@@ -323,6 +323,7 @@ int pard_estimate_drop_compact(const pard_plan_t* plan, int64_t n, int64_t max_s
     char* region = static_cast<char*>(d_workspace) + kHeaderBytes + marks_bytes(plan);
     char* stage = region + compact_workspace_bytes(n, plan->host.K);
     CompactArgs a{};
+    a.num_cus = plan->num_cus;
     a.num_segments = plan->host.K * plan->host.S;
     a.stages = plan->host.S;
     a.max_snapshot = max_snapshot_requests;
@@ -490,6 +491,7 @@ int pard_compact(const pard_plan_t* plan, int64_t n, int64_t max_snapshot_reques
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 255) != 0 ||
         workspace_bytes < kHeaderBytes + marks_bytes(plan) + compact_workspace_bytes(n, plan->host.K)) return PARD_E_WORKSPACE;
     CompactArgs a{};
+    a.num_cus = plan->num_cus;
     a.num_segments = plan->host.K * plan->host.S;
     a.stages = plan->host.S;
     a.max_snapshot = max_snapshot_requests;

@@ -706,8 +706,10 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
             // call with 64, 256 and 512 threads, most dropped / half kept: 50,000 snapshots of 60 under the bound 4096 580,
             // 620 and 674 us; 10,000 of 1500 236, 239 and 247 / 262, 253 and 259; 4096 of 3000 76, 77 and 80 / 107, 104 and
             // 103; 4096 of 4096 76, 76 and 80 / 118, 111 and 107; 2048 of 8192 74, 73 and 74 / 114, 108 and 104.
+            // So few snapshots that all their waves run at once are moved by four waves each whatever they hold (200 of 1000
+            // under 8192 21.8 us with one wave, 20.2 with eight; 50 of 50 no difference).
             if (a.n > 4096 * K) move_staged_kernel<512><<<(unsigned)K, 512, 0, stream>>>(a, snap_off);
-            else if (a.n > 2048 * K) move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
+            else if (a.n > 2048 * K || K <= 4 * a.num_cus) move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
             else move_staged_kernel<kWave><<<(unsigned)K, kWave, 0, stream>>>(a, snap_off);
             return hipGetLastError();
         }

@@ -262,6 +262,7 @@ struct CompactArgs {
     int32_t *surv_idx, *surv_ptr;
     uint32_t* status;
     void* workspace;
+    int32_t num_cus;
     // after an estimate call that counted and staged the survivors along the way (all three null otherwise):
     const uint32_t* kept;              // [K] survivors per snapshot
     const int32_t* staged;             // [n] a snapshot's survivors in queue order, from its first request's place on
