@@ -760,7 +760,11 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // first: estimate and compaction, shuffled, narrow and wide, 256 snapshots of 4000 32.3 and 25.2 us, 320 35.0 and 36.4,
     // 600 41.0 and 50.6; 256 of 8000 38.3 and 34.7, 300 45.0 and 50.7.  The smaller shapes gain for longer and less evenly:
     // 768 of 2000 (1.5 shares) 38.9 and 30.8, 1536 45.5 and 44.7; 1500 of 1000 35.0 and 32.1, 2048 36.4 and 38.5, 3000 49.9
-    // and 45.8; 3000 of 500 36.2 and 31.2, 4096 37.3 and 38.0.
+    // and 45.8; 3000 of 500 36.2 and 31.2, 4096 37.3 and 38.0.  Under a loose bound a snapshot may fit what a narrow
+    // workgroup takes at once, four requests a thread, and more threads only make the barriers longer: such batches stay
+    // narrow (shuffled, narrow and wide: 30 snapshots of 500 under the promised 4096 21.9 and 22.9 us, of 1100 23.8 and
+    // 22.4; of 2000 under 8192 20.1 and 20.5, of 3000 25.0 and 23.6; 2000 of 50 under 512 22.4 and 23.1), but not under
+    // sequentially consistent dropping up to 4096, where a queue's walk gains (30 of 1000 under 4096 23.4 and 21.8).
     //
     // The kernel for queue order is left out of small calls, where it is a launch more than it saves, in order or not (one
     // snapshot of a thousand 16.9 and 12.6 us in order, 15.9 and 14.0 shuffled; eight 19.4 and 15.1, 17.7 and 15.5; two of
@@ -769,6 +773,7 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // 29.8 with it, 30.6 without), but not under sequentially consistent dropping, where the wide workgroups are ahead of it
     // also in order: 100 snapshots of 5000, six stages, 36.0 and 32.0 us in order, 34.4 and 32.0 shuffled, of 8000 36.7 and
     // 34.4, 38.1 and 35.0.
+    const int narrow_threads = a.cap <= 512 ? 64 : a.cap <= 2048 ? 128 : a.cap <= 4096 ? 256 : 512;
     const int wide_threads = a.cap <= 512 ? 128 : a.cap <= 1024 ? 256 : a.cap <= 2048 ? 512 : 1024;
     const bool few = a.cap > 256 && (int64_t)a.plan.K * wide_threads <= 1024 * (int64_t)a.num_cus;
     const bool alone = few && (a.consistent || (a.cap <= 4096 && a.n <= 8192));
@@ -778,7 +783,7 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     } else {
         a.todo = nullptr;
     }
-    if (few) {
+    if (few && ((a.consistent && a.cap <= 4096) || a.n > 4 * narrow_threads * (int64_t)a.plan.K)) {
         if (a.cap <= 512) launch_capacity<512, 128>(a, stream);
         else if (a.cap <= 1024) launch_capacity<1024, 256>(a, stream);
         else if (a.cap <= 2048) launch_capacity<2048, 512>(a, stream);

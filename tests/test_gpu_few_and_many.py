@@ -45,6 +45,26 @@ def test_few_and_many(oracle_mod, K, per, kind):
     assert s.status_word() == 0
 
 
+@pytest.mark.parametrize("per,bound", [(1024, 4096), (1025, 4096), (2048, 8192), (2049, 8192), (100, 8192), (30, 300), (256, 512), (257, 512), (512, 2048), (513, 2048)])
+@pytest.mark.parametrize("kind", ["in-order", "low", "high"])
+def test_few_under_a_loose_bound(oracle_mod, per, bound, kind):
+    """Snapshots around what a narrow workgroup takes at once."""
+    from paper_2602_08747_amd import binding
+    w = wl.random_workload(per, K=9, S=3, n_per_snapshot=per, time_span=20 * per, slo_choices=(4 * per,) if kind == "in-order" else (3 * per, 6 * per),
+                           modes=(wl.MODE_HBF,) if kind == "high" else (wl.MODE_LBF,), dag_shared=1, vary_sizes=False)
+    w.lat_us[:] = np.maximum(1, w.lat_us // 20)
+    if kind == "in-order":
+        w = wl.in_deadline_order(w)
+    s = binding.Session(w, max_snapshot_requests=bound)
+    for consistent in (False, True):
+        ref = oracle_mod.run(w, threads=8, consistent=consistent)
+        s.run(consistent=consistent)
+        got = s.results()
+        for k in KEYS:
+            assert np.array_equal(got[k], ref[k]), (consistent, k)
+    assert s.status_word() == 0
+
+
 @pytest.mark.parametrize("K,per", [(2, 500), (3, 4000), (2, 8192), (300, 2100)])
 def test_many_stages(oracle_mod, K, per):
     from paper_2602_08747_amd import binding
