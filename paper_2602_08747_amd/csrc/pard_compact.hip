@@ -701,15 +701,16 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
         uint32_t* snap_off = kept + ((K * 4 + 255) & ~(int64_t)255) / 4;
         if (a.staged) {                              // counted and staged by the estimate kernels: only the move is left
             snapshot_offsets_kernel<<<1, 1024, 0, stream>>>(a.kept, K, snap_off);
-            // The width follows the snapshots' mean size, not the promised bound, which may be loose: a wave moves 1024
-            // survivors in one round, and a workgroup of four or eight for a few dozen costs more than it saves.  The whole
-            // call with 64, 256 and 512 threads, most dropped / half kept: 50,000 snapshots of 60 under the bound 4096 580,
-            // 620 and 674 us; 10,000 of 1500 236, 239 and 247 / 262, 253 and 259; 4096 of 3000 76, 77 and 80 / 107, 104 and
-            // 103; 4096 of 4096 76, 76 and 80 / 118, 111 and 107; 2048 of 8192 74, 73 and 74 / 114, 108 and 104.
-            // So few snapshots that all their waves run at once are moved by four waves each whatever they hold (200 of 1000
-            // under 8192 21.8 us with one wave, 20.2 with eight; 50 of 50 no difference).
-            if (a.n > 4096 * K) move_staged_kernel<512><<<(unsigned)K, 512, 0, stream>>>(a, snap_off);
-            else if (a.n > 2048 * K || K <= 4 * a.num_cus) move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
+            // One wave where the snapshots fill less than a quarter of the bound's workgroup on average: the bound is loose
+            // then, a wave moves 1024 survivors in one round, and a workgroup of four or eight for a few dozen costs more than
+            // it saves.  The whole call with 64, 256 and 512 threads, most dropped / half kept: 50,000 snapshots of 60 under
+            // the bound 4096 580, 620 and 674 us; 10,000 of 1500 under 8192 236, 239 and 247 / 262, 253 and 259; 4096 of 3000
+            // 76, 77 and 80 / 107, 104 and 103; 4096 of 4096 76, 76 and 80 / 118, 111 and 107; 2048 of 8192 74, 73 and 74 /
+            // 114, 108 and 104.  So few that all their waves run at once are moved by more waves whatever they hold (200 of
+            // 1000 under 8192 21.8 us with one, 20.2 with eight; 238 ragged up to 4601 27.2 with four, 25.8 with eight).
+            const bool few = K <= 4 * a.num_cus;
+            if (few ? a.max_snapshot >= 4096 : a.n > 4096 * K) move_staged_kernel<512><<<(unsigned)K, 512, 0, stream>>>(a, snap_off);
+            else if (few || a.n > (a.max_snapshot > 4096 ? 2048 : 1024) * K) move_staged_kernel<256><<<(unsigned)K, 256, 0, stream>>>(a, snap_off);
             else move_staged_kernel<kWave><<<(unsigned)K, kWave, 0, stream>>>(a, snap_off);
             return hipGetLastError();
         }

@@ -58,10 +58,10 @@ def test_staged_survivors_move(gpu, oracle_mod, per):
     agree(gpu, oracle_mod, w, one_call=True)
 
 
-@pytest.mark.parametrize("per,bound", [(40, 8192), (2048, 8192), (2049, 2049), (4096, 4096), (4097, 8192)])
+@pytest.mark.parametrize("per,bound", [(40, 8192), (1024, 4096), (1025, 4096), (2048, 8192), (2049, 2049), (2049, 8192), (4096, 4096), (4097, 8192)])
 @pytest.mark.parametrize("K", [3, 1100])
 def test_staged_survivors_move_by_mean_size(gpu, oracle_mod, per, bound, K):
-    """One wave, four or eight move a snapshot's survivors, by the mean size whatever bound is promised; at least four of few snapshots."""
+    """One wave, four or eight move a snapshot's survivors, by the mean size beside the promised bound; at least four of few snapshots."""
     w = mixed(per, K, 4, per, dag_shared=1, vary_sizes=False)
     agree(gpu, oracle_mod, w, bound, one_call=True)
 
