@@ -714,20 +714,17 @@ __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     else snapshot_body<T, CAP, SCAP, false, CONSISTENT, AHEAD>(A, L, u, lo, m, aligned, off);
 }
 
-// Sequentially consistent: positions in time ahead of the walk (AHEAD) at the largest capacity, from a mean of more than 1024
-// requests per queue on; 512 with the wide workgroups of few snapshots, where a call takes as long as one chain.  With the
-// compaction, the look of the kernel for queue order left out, 3000 snapshots of 8000 in overload / half of them kept, plain
-// walk and ahead: one queue each 580 / 613 and 371 / 373 us, three 309 / 336 and 274 / 287, six 261 / 288 and 264 / 276, eight
-// (1000 requests each) 240 / 269 and 255 / 273; six of 250 under the same promised bound 415 / 417 and 444 / 422.  Smaller
-// capacities: 6000 snapshots of 3500 in overload 253 and 287, 10,000 of 1000 90 and 105.  Wide, 100 snapshots: 1000 a queue
-// 36.3 / 37.5 and 35.1 / 35.2, 667 33.9 / 35.1 and 35.0 / 34.5, 417 31.2 / 31.5 and 33.3 / 31.9, 100 21.6 / 21.6 and 24.1 / 22.9.
-constexpr int64_t kAheadQueue = 1024, kAheadQueueWide = 512;
-
+// Sequentially consistent: positions in time ahead of the walk (AHEAD) at the largest capacity, unless the snapshots fill less
+// than a quarter of it on average: then the promised bound is loose and the queues are short (12,000 snapshots of 1500 under
+// 8192, plain walk and ahead 415 and 444 us).  A snapshot takes as long as its longest queue, and how long that is only the
+// device knows.  With the compaction, shuffled, in overload: 3000 snapshots of 8000 in one queue 580 and 371 us, in three 309
+// and 274; ragged, up to 7000, six stages alike 195 and 213 (with the look), skewed 322 and 284;
+// twelve 190 and 215, skewed 351 and 321.
+// Smaller capacities: 6000 snapshots of 3500 in overload 253 and 287, 10,000 of 1000 90 and 105.
 template <int CAP, int T, int SCAP>
 void launch_stages(const FusedArgs& a, hipStream_t stream) {
     if constexpr (CAP == PARD_FUSED_SNAPSHOT_CAPACITY)
-        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF &&
-            a.n > (T > 512 ? kAheadQueueWide : kAheadQueue) * a.plan.K * a.plan.S) {
+        if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF && a.n > CAP / 4 * (int64_t)a.plan.K) {
             fused_snapshot_kernel<T, CAP, SCAP, true, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
             return;
         }
@@ -760,30 +757,32 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // first: estimate and compaction, shuffled, narrow and wide, 256 snapshots of 4000 32.3 and 25.2 us, 320 35.0 and 36.4,
     // 600 41.0 and 50.6; 256 of 8000 38.3 and 34.7, 300 45.0 and 50.7.  The smaller shapes gain for longer and less evenly:
     // 768 of 2000 (1.5 shares) 38.9 and 30.8, 1536 45.5 and 44.7; 1500 of 1000 35.0 and 32.1, 2048 36.4 and 38.5, 3000 49.9
-    // and 45.8; 3000 of 500 36.2 and 31.2, 4096 37.3 and 38.0.  Under a loose bound a snapshot may fit what a narrow
-    // workgroup takes at once, four requests a thread, and more threads only make the barriers longer: such batches stay
-    // narrow (shuffled, narrow and wide: 30 snapshots of 500 under the promised 4096 21.9 and 22.9 us, of 1100 23.8 and
-    // 22.4; of 2000 under 8192 20.1 and 20.5, of 3000 25.0 and 23.6; 2000 of 50 under 512 22.4 and 23.1), but not under
-    // sequentially consistent dropping up to 4096, where a queue's walk gains (30 of 1000 under 4096 23.4 and 21.8).
+    // and 45.8; 3000 of 500 36.2 and 31.2, 4096 37.3 and 38.0.  Snapshots that fill less than a quarter of the capacity on
+    // average (a loose bound; ragged sizes up to the bound fill more) fit what a narrow workgroup takes at once, and more
+    // threads only make the barriers longer: they stay narrow (30 snapshots of 500 under the promised 4096 21.9 and 22.9 us,
+    // of 1100 23.8 and 22.4; of 2000 under 8192 20.1 and 20.5, of 3000 25.0 and 23.6; 2000 of 50 under 512 22.4 and 23.1),
+    // but not under sequentially consistent dropping up to 4096, where a queue's walk gains (30 of 1000 under 4096 23.4 and
+    // 21.8).
     //
     // The kernel for queue order is left out of small calls, where it is a launch more than it saves, in order or not (one
     // snapshot of a thousand 16.9 and 12.6 us in order, 15.9 and 14.0 shuffled; eight 19.4 and 15.1, 17.7 and 15.5; two of
     // 4000 19.5 and 18.2, 20.5 and 18.3).  The limit says what is taken for small, it is not a crossing: the difference is
     // the same at 256 snapshots of a thousand (23.1 and 19.1).  The largest capacity keeps the kernel (200 of 8000 in order
-    // 29.8 with it, 30.6 without), but not under sequentially consistent dropping, where the wide workgroups are ahead of it
-    // also in order: 100 snapshots of 5000, six stages, 36.0 and 32.0 us in order, 34.4 and 32.0 shuffled, of 8000 36.7 and
-    // 34.4, 38.1 and 35.0.
-    const int narrow_threads = a.cap <= 512 ? 64 : a.cap <= 2048 ? 128 : a.cap <= 4096 ? 256 : 512;
+    // 29.8 with it, 30.6 without); under sequentially consistent dropping the wide workgroups are ahead of it up to about
+    // 3000 requests a snapshot (100 snapshots in order, six stages alike / most requests in one of them, with it and
+    // without: ragged up to 4400 37.6 / 42.3 and 31.6 / 40.9, 5500 39.8 / 44.4 and 33.9 / 44.2, 8192 45.2 / 51.8 and 41.9 /
+    // 62.2).
+    const int capacity = a.cap <= 512 ? 512 : a.cap <= 1024 ? 1024 : a.cap <= 2048 ? 2048 : a.cap <= 4096 ? 4096 : 8192;
     const int wide_threads = a.cap <= 512 ? 128 : a.cap <= 1024 ? 256 : a.cap <= 2048 ? 512 : 1024;
     const bool few = a.cap > 256 && (int64_t)a.plan.K * wide_threads <= 1024 * (int64_t)a.num_cus;
-    const bool alone = few && (a.consistent || (a.cap <= 4096 && a.n <= 8192));
+    const bool alone = few && (a.consistent ? a.n <= 3072 * (int64_t)a.plan.K : a.cap <= 4096 && a.n <= 8192);
     if (!alone && presorted_path_covers(a)) {
         const hipError_t e = launch_presorted(a, stream);
         if (e != hipSuccess) return e;
     } else {
         a.todo = nullptr;
     }
-    if (few && ((a.consistent && a.cap <= 4096) || a.n > 4 * narrow_threads * (int64_t)a.plan.K)) {
+    if (few && ((a.consistent && a.cap <= 4096) || a.n > capacity / 4 * (int64_t)a.plan.K)) {
         if (a.cap <= 512) launch_capacity<512, 128>(a, stream);
         else if (a.cap <= 1024) launch_capacity<1024, 256>(a, stream);
         else if (a.cap <= 2048) launch_capacity<2048, 512>(a, stream);

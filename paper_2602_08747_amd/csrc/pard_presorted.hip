@@ -491,12 +491,12 @@ __global__ __launch_bounds__(T, PARD_PS_WAVES) void presorted_snapshot_kernel(Fu
 // requests, and below about half of that the general kernel's smaller capacities are as fast or faster (65,536
 // snapshots of 256 in queue order: 0.210 ms per call through this kernel, 0.148 through the general one; of 512:
 // 0.234 either way; 43,690 of 768: 0.181 against 0.270).  Sequentially consistent: only the largest workgroup, and
-// only where the snapshots fill more than half of it on average; the promised bound alone may be loose.  With the compaction,
-// six stages, in queue order / shuffled, without this kernel and with it: 3000 snapshots of 8000 in overload 240 / 264 and
-// 187 / 274 us, 4000 of 4500 245 / 243 and 215 / 257; 12,000 of 1500 under the bound 8192 412 / 415 and 505 / 443; 6000 of up
-// to 3500 under their own bound gained 15 us in order and lost 12 otherwise.
+// only where the snapshots fill more than a quarter of it on average (below that the promised bound is loose).  With the
+// compaction, six stages, in queue order / shuffled, without this kernel and with it: 3000 snapshots of 8000 in overload 240 /
+// 264 and 187 / 274 us, 4000 of 4500 245 / 263 and 215 / 276; 12,000 of 1500 under the bound 8192 438 / 444 and 505 / 474; 6000
+// of up to 3500 under their own bound gained 15 us in order and lost 12 otherwise.
 bool presorted_path_covers(const FusedArgs& a) {
-    if (a.consistent && (a.cap <= 4096 || a.n <= (int64_t)4096 * a.plan.K)) return false;
+    if (a.consistent && (a.cap <= 4096 || a.n <= PARD_FUSED_SNAPSHOT_CAPACITY / 4 * (int64_t)a.plan.K)) return false;
     return a.todo != nullptr && a.plan.presorted_ok && a.plan.uniform_mode == PARD_ORDER_LBF &&
            a.plan.S <= kPresortedMaxStages && a.cap > 512 && a.cap <= PARD_FUSED_SNAPSHOT_CAPACITY;
 }

@@ -92,15 +92,22 @@ CASES = {
 }
 
 
-CASES.update({   # more than 1024 requests per queue (512 of few snapshots), so that the general kernel forms the positions ahead of the walk
+def some_short(sizes, **kw):
+    """Snapshots of these sizes, the first the largest and above half of the capacity."""
+    w = wl.random_workload(sum(sizes), K=len(sizes), S=4, n_per_snapshot=max(sizes), time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000),
+                           vary_sizes=False, **kw)
+    return wl.with_snapshot_sizes(w, sizes)
+
+
+CASES.update({
     "not-in-order-long": lambda: wl.random_workload(21, K=3, S=6, n_per_snapshot=8000, time_span=160_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000, 400_000), vary_sizes=False),
     "not-in-order-many": lambda: wl.random_workload(22, K=257, S=3, n_per_snapshot=4100, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), dag_shared=1, vary_sizes=False),
     "seven-stages-long": lambda: queued(23, 2, 7, 8192, vary_sizes=False),
     "falling-tables-long": lambda: falling(queued(24, 2, 5, 6000, vary_sizes=False)),
-    "just-ahead": lambda: wl.random_workload(25, K=2, S=4, n_per_snapshot=4097, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
-    "just-ahead-wide": lambda: wl.random_workload(26, K=2, S=8, n_per_snapshot=4097, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
-    "just-not-ahead-wide": lambda: wl.random_workload(26, K=2, S=8, n_per_snapshot=4096, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
-    "just-not-ahead": lambda: wl.random_workload(25, K=2, S=4, n_per_snapshot=4096, time_span=82_000, modes=(wl.MODE_LBF,), slo_choices=(60_000, 200_000), vary_sizes=False),
+    "mean-2049": lambda: some_short([4097, 1366, 1366, 1367]),            # more than a quarter of the capacity on average,
+    "mean-2048": lambda: some_short([4097, 1365, 1365, 1365]),            # and no more
+    "mean-2049-in-order": lambda: wl.in_deadline_order(some_short([4097, 1366, 1366, 1367])),
+    "mean-2048-in-order": lambda: wl.in_deadline_order(some_short([4097, 1365, 1365, 1365])),
 })
 
 
@@ -136,12 +143,12 @@ def test_consistent_on_chip(oracle_mod, which, least):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("K,S,per,bound,tried", [(257, 2, 4097, 8192, True), (257, 2, 4096, 8192, False), (300, 6, 300, 8192, False),
-                                                     (256, 2, 4097, 8192, False), (3, 2, 8000, 8192, False)])
+@pytest.mark.parametrize("K,S,per,bound,tried", [(257, 2, 2049, 8192, True), (257, 2, 2048, 8192, False), (300, 6, 300, 8192, False),
+                                                     (256, 2, 3072, 8192, False), (256, 2, 3073, 8192, True), (3, 2, 8000, 8192, True)])
 def test_in_order_kernel_by_mean_size(oracle_mod, K, S, per, bound, tried):
-    """The kernel for queue order is tried where snapshots fill more than half of its workgroup on average, whatever bound is
-    promised, and are too many for the wide workgroups: it leaves a mark per snapshot behind the workspace's 256-byte header, and
-    nothing else writes there."""
+    """The kernel for queue order is tried where snapshots fill more than a quarter of its workgroup on average, whatever bound is
+    promised (more than 3072 requests where the wide workgroups would take them): it leaves a mark per snapshot behind the
+    workspace's 256-byte header, and nothing else writes there."""
     from paper_2602_08747_amd import binding
     w = queued(per + K, K, S, per, vary_sizes=False, dag_shared=1)
     ref = oracle_mod.run(w, threads=8, consistent=True)
@@ -199,4 +206,4 @@ def test_positions_in_time_at_every_step(oracle_mod, most, least, shuffled):
     got = s.results()
     for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
         assert np.array_equal(got[k], ref[k]), k
-    assert (s.workspace[64:64 + w.K].cpu().numpy() == (-5 if most >= 1 << 17 or least == 1 else int(shuffled))).all()
+    assert (s.workspace[64:64 + w.K].cpu().numpy() == (-5 if most >= 1 << 17 else int(shuffled))).all()

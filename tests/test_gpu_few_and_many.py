@@ -45,10 +45,10 @@ def test_few_and_many(oracle_mod, K, per, kind):
     assert s.status_word() == 0
 
 
-@pytest.mark.parametrize("per,bound", [(1024, 4096), (1025, 4096), (2048, 8192), (2049, 8192), (100, 8192), (30, 300), (256, 512), (257, 512), (512, 2048), (513, 2048)])
+@pytest.mark.parametrize("per,bound", [(1024, 4096), (1025, 4096), (2048, 8192), (2049, 8192), (100, 8192), (30, 300), (128, 512), (129, 512), (256, 1024), (257, 1024), (512, 2048), (513, 2048)])
 @pytest.mark.parametrize("kind", ["in-order", "low", "high"])
 def test_few_under_a_loose_bound(oracle_mod, per, bound, kind):
-    """Snapshots around what a narrow workgroup takes at once."""
+    """Snapshots around a quarter of the capacity."""
     from paper_2602_08747_amd import binding
     w = wl.random_workload(per, K=9, S=3, n_per_snapshot=per, time_span=20 * per, slo_choices=(4 * per,) if kind == "in-order" else (3 * per, 6 * per),
                            modes=(wl.MODE_HBF,) if kind == "high" else (wl.MODE_LBF,), dag_shared=1, vary_sizes=False)
