@@ -213,7 +213,7 @@ static int estimate_drop_impl(const pard_plan_t* plan, int64_t n, int64_t max_sn
                               const int32_t* d_snap_ptr, const int32_t* d_now, const int64_t* d_sub, bool consistent,
                               int32_t* d_est, uint8_t* d_drop, int32_t* d_order, int32_t* d_seg_ptr,
                               void* d_workspace, int64_t workspace_bytes, void* stream, bool own_buffer = false,
-                              bool stage_survivors = false) {
+                              bool stage_survivors = false, const uint32_t** ranked_todo = nullptr) {
     if (!plan || !d_snap_ptr || !d_now || !d_seg_ptr) return PARD_E_NULL;
     if (n < 0 || n >= ((int64_t)1 << 30) || max_snapshot_requests < 0) return PARD_E_BAD_SHAPE;
     if (n > 0 && (!d_deadline || !d_stage || !d_est || !d_drop || !d_order)) return PARD_E_NULL;
@@ -249,6 +249,10 @@ static int estimate_drop_impl(const pard_plan_t* plan, int64_t n, int64_t max_sn
         a.consistent = consistent ? 1 : 0;
         a.n = n;
         a.num_cus = plan->num_cus;
+        if (ranked_todo && plan->host.S > 1) {       // (one stage: the plain estimates are the ranked ones)
+            a.ranked = 1;
+            if (tries_queue_order(a)) *ranked_todo = a.todo;
+        }
         e = launch_fused(a, s);
     } else {
         SortArgs a{};
@@ -362,10 +366,12 @@ int pard_estimate_drop_ranked(const pard_plan_t* plan, int64_t n, int64_t max_sn
                               const int32_t* d_snap_ptr, const int32_t* d_now,
                               int32_t* d_est, uint8_t* d_drop, int32_t* d_order, int32_t* d_seg_ptr,
                               void* d_workspace, int64_t workspace_bytes, void* stream) {
+    const uint32_t* todo = nullptr;
     const int rc = estimate_drop_impl(plan, n, max_snapshot_requests, d_arrival, d_deadline, d_stage, d_snap_ptr, d_now, nullptr,
-                                      false, d_est, d_drop, d_order, d_seg_ptr, d_workspace, workspace_bytes, stream);
+                                      false, d_est, d_drop, d_order, d_seg_ptr, d_workspace, workspace_bytes, stream, false, false, &todo);
     if (rc != PARD_OK) return rc;
     RankedArgs a{};
+    a.todo = todo;
     a.plan = plan->dev;
     a.n = n;
     a.deadline = d_deadline; a.now = d_now;

@@ -210,10 +210,14 @@ struct FusedArgs {
     int32_t* loc_ptr;                  // [K*S] out: survivors of the snapshot before each of its queues
     int32_t cap;                       // promised bound on a snapshot's size
     int32_t consistent;                // positions count only the kept requests ahead
+    int32_t ranked;                    // launch_ranked follows: the kernel for queue order forms the ranked estimates of what it finishes,
+                                       // the general one only the queues
     int64_t n;                         // total requests (bounds every index derived from snap_ptr)
     int32_t num_cus;
 };
 hipError_t launch_fused(const FusedArgs& a, hipStream_t stream);
+// Whether launch_fused lets the kernel for queue order try first (todo[] then says which snapshots it left).
+bool tries_queue_order(const FusedArgs& a);
 // Snapshots whose requests already come in queue order (launch_fused tries this first when it applies).
 constexpr int kPresortedMaxStages = 6;
 bool presorted_path_covers(const FusedArgs& a);
@@ -247,6 +251,7 @@ struct RankedArgs {
     const int32_t *order, *seg_ptr;    // the plain call's queues
     int32_t* est;                      // rewritten
     uint8_t* drop;
+    const uint32_t* todo;              // [K], or null: only the snapshots marked here are still plain
     int64_t max_snapshot;              // promised bound on a snapshot's size
     int32_t num_cus;
 };

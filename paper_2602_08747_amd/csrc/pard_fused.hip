@@ -72,7 +72,7 @@ constexpr int log2_of(int x) { return x <= 1 ? 0 : 1 + log2_of(x / 2); }
 // start, so no per-request bounds test is needed.
 template <int T, int CAP, int SCAP, bool FULL, bool CONSISTENT, bool AHEAD>
 __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CAP, SCAP, T>& L, const int u, const int64_t lo,
-                                              const int m, const bool aligned, const int off) {
+                                              const int m, const bool aligned, const int off, const bool results) {
     constexpr int kCap = CAP;
     constexpr int kIdxBits = log2_of(CAP);                 // bits of a local index
     constexpr int kCntWords = SnapshotLds<CAP, SCAP, T>::kCntWords;
@@ -540,7 +540,7 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
     const bool quick = !wide && L.slow_stages == 0u;          // every stage admits the exact short-queue form
 #pragma unroll
     for (int g = 0; g < (CONSISTENT ? 0 : G); ++g) {
-        if (dead_group(g)) continue;
+        if (!results || dead_group(g)) continue;
         const int base = (g * T + tid) * 4;
         int32_t est[4];
         uint8_t drp[4];
@@ -680,7 +680,10 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
     if (tid == 0) A.kept[u] = total;
 }
 
-template <int T, int CAP, int SCAP, bool CONSISTENT, bool AHEAD>
+// QUEUES: a kernel behind this one forms the estimates of every snapshot within the promise (ranked positions), here only the
+// queues are wanted: 3000 snapshots of up to 8000, shuffled, ranked, with the compaction 356 -> 343 us; 12,000 of up to 1000 206 ->
+// 200.  A form of its own: as a condition in the plain one it took six registers more there (spilled; 0.5 % of the plain call).
+template <int T, int CAP, int SCAP, bool CONSISTENT, bool AHEAD, bool QUEUES>
 __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = CAP;
     __shared__ SnapshotLds<CAP, SCAP, T> L;
@@ -705,13 +708,14 @@ __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     const uintptr_t bits = reinterpret_cast<uintptr_t>(A.deadline) | reinterpret_cast<uintptr_t>(A.stage) |
                            reinterpret_cast<uintptr_t>(A.est) | reinterpret_cast<uintptr_t>(A.order) |
                            (reinterpret_cast<uintptr_t>(A.drop) << 2);
+    const bool results = !QUEUES || hi - lo > limit;
     // 16-byte accesses need aligned arrays; the snapshot's own start is taken care of by shifting the
     // local indices by lo mod 4, as long as the shifted snapshot still fits the capacity
     const int shift = (int)(lo & 3);
     const bool aligned = (bits & 15) == 0 && m + shift <= kCap;
     const int off = aligned ? shift : 0;
-    if (m == kCap && aligned && off == 0) snapshot_body<T, CAP, SCAP, true, CONSISTENT, AHEAD>(A, L, u, lo, m, true, 0);
-    else snapshot_body<T, CAP, SCAP, false, CONSISTENT, AHEAD>(A, L, u, lo, m, aligned, off);
+    if (m == kCap && aligned && off == 0) snapshot_body<T, CAP, SCAP, true, CONSISTENT, AHEAD>(A, L, u, lo, m, true, 0, results);
+    else snapshot_body<T, CAP, SCAP, false, CONSISTENT, AHEAD>(A, L, u, lo, m, aligned, off, results);
 }
 
 // Sequentially consistent: positions in time ahead of the walk (AHEAD) at the largest capacity, unless the snapshots fill less
@@ -725,11 +729,12 @@ template <int CAP, int T, int SCAP>
 void launch_stages(const FusedArgs& a, hipStream_t stream) {
     if constexpr (CAP == PARD_FUSED_SNAPSHOT_CAPACITY)
         if (a.consistent && a.plan.uniform_mode == PARD_ORDER_LBF && a.n > CAP / 4 * (int64_t)a.plan.K) {
-            fused_snapshot_kernel<T, CAP, SCAP, true, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+            fused_snapshot_kernel<T, CAP, SCAP, true, true, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
             return;
         }
-    if (a.consistent) fused_snapshot_kernel<T, CAP, SCAP, true, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
-    else fused_snapshot_kernel<T, CAP, SCAP, false, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+    if (a.consistent) fused_snapshot_kernel<T, CAP, SCAP, true, false, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+    else if (a.ranked) fused_snapshot_kernel<T, CAP, SCAP, false, false, true><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
+    else fused_snapshot_kernel<T, CAP, SCAP, false, false, false><<<dim3((unsigned)a.plan.K), dim3(T), 0, stream>>>(a);
 }
 
 template <int CAP, int T>
@@ -743,6 +748,17 @@ void launch_capacity(const FusedArgs& a, hipStream_t stream) {
 }
 
 }  // namespace
+
+namespace {
+int wide_threads(int32_t cap) { return cap <= 512 ? 128 : cap <= 1024 ? 256 : cap <= 2048 ? 512 : 1024; }
+bool few_snapshots(const FusedArgs& a) { return a.cap > 256 && (int64_t)a.plan.K * wide_threads(a.cap) <= 1024 * (int64_t)a.num_cus; }
+}  // namespace
+
+bool tries_queue_order(const FusedArgs& a) {
+    if (wave_path_covers(a)) return false;
+    const bool alone = few_snapshots(a) && (a.consistent ? a.n <= 3072 * (int64_t)a.plan.K : a.cap <= 4096 && a.n <= 8192);
+    return !alone && presorted_path_covers(a);
+}
 
 hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     FusedArgs a = args;
@@ -773,10 +789,8 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // without: ragged up to 4400 37.6 / 42.3 and 31.6 / 40.9, 5500 39.8 / 44.4 and 33.9 / 44.2, 8192 45.2 / 51.8 and 41.9 /
     // 62.2).
     const int capacity = a.cap <= 512 ? 512 : a.cap <= 1024 ? 1024 : a.cap <= 2048 ? 2048 : a.cap <= 4096 ? 4096 : 8192;
-    const int wide_threads = a.cap <= 512 ? 128 : a.cap <= 1024 ? 256 : a.cap <= 2048 ? 512 : 1024;
-    const bool few = a.cap > 256 && (int64_t)a.plan.K * wide_threads <= 1024 * (int64_t)a.num_cus;
-    const bool alone = few && (a.consistent ? a.n <= 3072 * (int64_t)a.plan.K : a.cap <= 4096 && a.n <= 8192);
-    if (!alone && presorted_path_covers(a)) {
+    const bool few = few_snapshots(a);
+    if (tries_queue_order(a)) {
         const hipError_t e = launch_presorted(a, stream);
         if (e != hipSuccess) return e;
     } else {

@@ -28,6 +28,7 @@
 //      slot, in how many positions its requests are in time, one wave per queue turns those into positions and decisions
 //      (a prefix minimum per 64 requests), and the estimates are formed from the positions.
 #include "pard_device.hpp"
+#include <type_traits>
 
 namespace pard {
 
@@ -49,7 +50,7 @@ constexpr int kPsStages = kPresortedMaxStages;     // 3-bit count fields of stag
 constexpr uint32_t kDeadStage = 7;
 constexpr int kPsEntries = 128;                    // path entries of a DAG kept in LDS (longer lists are read in place)
 
-template <int T, bool CONS>
+template <int T, bool CONS, bool RANKED>
 struct PresortedLds {
     static constexpr int CAP = 16 * T;
     static constexpr int SUB = T / kWave * 4;                 // sub-blocks of 256 requests
@@ -70,6 +71,8 @@ struct PresortedLds {
     uint16_t chain[CONS ? CAP : 1];                           // sequentially consistent, by queue slot: positions the request is in time
                                                               // at, then its position | drop << 15
     float inv[8];                                             // sequentially consistent: W / lat[B] per stage
+    uint32_t run_end[RANKED ? SUB : 1][3];                    // ranked: per sub-block, 1 where a run of equal deadlines ends in it, and the
+                                                              // requests per stage up to the first such end (10-bit fields)
     uint32_t verdict;                                         // 0: in order and finished here, 1: left to the general kernel
 };
 
@@ -78,12 +81,120 @@ __device__ __forceinline__ int32_t from_previous_lane(int32_t v, int32_t own) {
     return __builtin_amdgcn_update_dpp(own, v, 0x138, 0xF, 0xF, false);               // wave_shr:1
 }
 
+// One more request of stage k (none for slots that are not live) in two words of three 10-bit fields.
+__device__ __forceinline__ void count_request(uint32_t k, uint32_t& n0, uint32_t& n1) {
+    constexpr uint32_t kShifts = 10u << 5 | 20u << 10 | 10u << 20 | 20u << 25;              // 0, 10, 20, 0, 10, 20
+    const uint32_t one = k < (uint32_t)kPsStages ? 1u << ((kShifts >> (5u * k)) & 31u) : 0u;
+    n0 += k < 3u ? one : 0u;
+    n1 += k < 3u ? 0u : one;
+}
+
+// Ranked estimates of a lane's four requests of sub-block `sub`.  In a later queue the requests that come first are the ones
+// with a deadline up to one's own.  The snapshot is in deadline order, so these are the earlier requests of that stage and
+// the ones that share the deadline: counted up to the end of the run of equal deadlines, which lies among the lane's own
+// four, at the first end in a lane above, or at the first end of a later sub-block.  Then the stages in an order in which
+// successors come first: cost at that place plus the most any successor still takes.  The own stage's position counts the
+// earlier requests only, and what its own place in that order yields is the estimate.  Saturating 32-bit sums are enough:
+// 2^32 - 1 is past INT32_MAX as an estimate and past every deadline that can be exceeded.  Bound by vector instructions
+// (230 per request, of which about 150 here; 85 % of the issue slots).  4096 snapshots of 8192 in order, six stages: 240 us for
+// this kernel against 115 + 356 for the plain one and ranked_queues_kernel behind it, the call with the compaction 511 -> 289;
+// 12,000 of up to 1000 167 -> 151; 100 of 8000, three stages, 60 -> 32.
+template <int T>
+__device__ __forceinline__ void ranked_estimates(const PresortedLds<T, false, true>& L, const int S, const int sub, const int lane, uint32_t sr,
+                                                 uint32_t ex0, uint32_t ex1, uint32_t ends, const uint32_t with_end,
+                                                 const uint32_t (&topo)[kPsStages], uint32_t (&e32)[4]) {
+    // (nothing of the next sub-block is formed while this one's sums are held)
+    asm volatile("" : "+v"(sr), "+v"(ex0), "+v"(ex1), "+v"(ends));
+    uint32_t k[4], n0[4], n1[4];             // requests per stage of the sub-block before a request: those ahead of it, unless it has ties
+    uint32_t a0 = ex0, a1 = ex1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        k[c] = (sr >> (8 * c)) & 7u;
+        n0[c] = a0;
+        n1[c] = a1;
+        count_request(k[c], a0, a1);
+    }
+    uint32_t across = 0, row = (uint32_t)sub;               // bit c: the run of request c ends in sub-block `row`
+    if (__ballot(ends != 15u) != 0ull) {
+        // up to and including the lane's first end
+        const unsigned long long any = __ballot(ends != 0u);
+        uint32_t f0 = a0, f1 = a1;
+#pragma unroll
+        for (int c = 2; c >= 0; --c)
+            if ((ends >> c) & 1u) { f0 = n0[c + 1]; f1 = n1[c + 1]; }
+        const unsigned long long above = lane < kWave - 1 ? any >> (lane + 1) : 0ull;
+        const int from = above ? lane + 1 + __builtin_ctzll(above) : lane;
+        f0 = (uint32_t)__shfl((int)f0, from);
+        f1 = (uint32_t)__shfl((int)f1, from);
+        bool far = above == 0ull;
+        if (far) {                                           // (the last slot of all ends a run: there is a later sub-block)
+            const uint32_t later = sub < 31 ? with_end >> (sub + 1) : 0u;
+            row = later ? (uint32_t)sub + 1u + (uint32_t)__builtin_ctz(later) : (uint32_t)sub;
+            f0 = L.run_end[row][1];
+            f1 = L.run_end[row][2];
+        }
+#pragma unroll
+        for (int c = 3; c >= 0; --c) {
+            if ((ends >> c) & 1u) {                          // ends its run: nothing shares its deadline behind it
+                f0 = n0[c];
+                f1 = n1[c];
+                count_request(k[c], f0, f1);
+                far = false;
+            } else {                                         // up to the run's end, in the own queue the earlier ones only
+                const uint32_t field = k[c] < (uint32_t)kPsStages ? 1023u << (10u * (k[c] < 3u ? k[c] : k[c] - 3u)) : 0u;
+                const uint32_t keep0 = k[c] < 3u ? field : 0u, keep1 = k[c] < 3u ? 0u : field;
+                n0[c] = (f0 & ~keep0) | (n0[c] & keep0);
+                n1[c] = (f1 & ~keep1) | (n1[c] & keep1);
+                across |= far ? 1u << c : 0u;
+            }
+        }
+    }
+    // Away from the front of the queues (nobody here in a first batch) and with no run that leaves the sub-block, the
+    // execution latency is the full batch's and the counts need no other row: two forms of the same steps.
+    const bool front = lane < S && (uint32_t)L.first_slot[sub][lane] - L.quick[lane][5] < L.quick[lane][0];
+    auto stages = [&](auto plain_tag) {
+        constexpr bool PLAIN = decltype(plain_tag)::value;
+        uint32_t behind[kPsStages][4];       // by place: from that stage on to the end, on the longest way
+#pragma unroll
+        for (int p = 0; p < kPsStages; ++p) {
+            if (p >= S) break;
+            asm volatile("" ::: "memory");   // one stage's constants at a time
+            const uint32_t s = topo[p] & 0xFFu, shift = 10u * (s < 3u ? s : s - 3u);
+            const uint4 qa = *reinterpret_cast<const uint4*>(&L.quick[s][0]);     // B-1, 1/B, 1/W, aW
+            const uint2 qb = *reinterpret_cast<const uint2*>(&L.quick[s][4]);     // bW, queue start
+            // fma(x, r, r / 2) is (x + 1/2) r rounded once, as the product of the exact x + 1/2 is
+            const float rB = __uint_as_float(qa.y), rW = __uint_as_float(qa.z), hB = 0.5f * rB, hW = 0.5f * rW;
+            const uint32_t from = (uint32_t)L.first_slot[sub][s] - qb.y + qa.x;
+            const uint32_t* lat = &L.lat[s * PARD_LAT_ENTRIES];
+            const uint32_t full = lat[qa.x];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bool own = k[c] == s;
+                uint32_t x = (((s < 3u ? n0[c] : n1[c]) >> shift) & 1023u) + from;        // requests ahead + B - 1
+                if (!PLAIN && !own && ((across >> c) & 1u)) x += (uint32_t)L.first_slot[row][s] - (uint32_t)L.first_slot[sub][s];
+                const uint32_t q = (uint32_t)__builtin_fmaf((float)x, rB, hB);
+                const uint32_t wait = __umul24(q, qa.w) + (uint32_t)__builtin_fmaf((float)__umul24(q, qb.x), rW, hW);
+                const uint32_t cost = wait + (PLAIN ? full : lat[x < 2u * qa.x ? x - qa.x : qa.x]);
+                uint32_t most = 0;
+#pragma unroll
+                for (int t = 0; t < p; ++t)
+                    if ((topo[p] >> (16 + t)) & 1u) most = behind[t][c] > most ? behind[t][c] : most;
+                behind[p][c] = __builtin_elementwise_add_sat(cost, most);
+                e32[c] = own ? behind[p][c] : e32[c];
+            }
+        }
+    };
+    if (__ballot(across != 0u || front) == 0ull) stages(std::true_type{});
+    else stages(std::false_type{});
+}
+
 // FULL: the snapshot holds exactly 16 T requests and every array is 16-byte aligned at its start.
 // CONS: sequentially consistent dropping (positions count the kept requests ahead, Section 4.1).
-template <int T, bool FULL, bool CONS>
-__device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<T, CONS>& L, const int u, const int64_t lo,
+// RANKED: in a later queue a request stands where its deadline puts it (see the header of pard_ranked.hip).
+template <int T, bool FULL, bool CONS, bool RANKED>
+__device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<T, CONS, RANKED>& L, const int u, const int64_t lo,
                                                const int m, const bool aligned, const int off) {
-    constexpr int SUB = PresortedLds<T, CONS>::SUB;
+    constexpr int SUB = PresortedLds<T, CONS, RANKED>::SUB;
     const PlanDev& P = A.plan;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -125,7 +236,7 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     // memory a chain of dependent loads, one per stage of a path.  They are fetched here, behind the request loads.
     const int e_lo = P.dag_entry_ptr[dag], n_entries = P.dag_entry_ptr[dag + 1] - e_lo;
     const bool entries_cached = n_entries <= kPsEntries;
-    if (entries_cached)
+    if (!RANKED && entries_cached)
         for (int e = tid; e < n_entries; e += T)
             L.ent[e] = (uint32_t)P.entry_stage[e_lo + e] | ((uint32_t)(P.entry_end[e_lo + e] - e_lo) << 8);
     {
@@ -181,6 +292,30 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     if (lane == 0) L.disorder[wave] = wave_saw_fall ? 1u : 0u;
     __syncthreads();
 
+    // ---- ranked: where the runs of equal deadlines end ---------------------------------------
+    uint32_t ends = 0;                      // bit 4 j + c: the next request's deadline is another one
+    if (RANKED) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int sub = wave * 4 + j;
+            int32_t after = __builtin_amdgcn_update_dpp(0, dl[j][0], 0x130, 0xF, 0xF, false);       // wave_shl:1, the next lane's first
+            if (lane == kWave - 1) after = sub + 1 < SUB ? L.edge_lo[sub + 1] : ~dl[j][3];          // nothing lies behind the last
+            const uint32_t b = (dl[j][0] != dl[j][1] ? 1u : 0u) | (dl[j][1] != dl[j][2] ? 2u : 0u) |
+                               (dl[j][2] != dl[j][3] ? 4u : 0u) | (dl[j][3] != after ? 8u : 0u);
+            ends |= b << (4 * j);
+            const unsigned long long any = __ballot(b != 0u);
+            if (any == 0ull ? lane == 0 : lane == __builtin_ctzll(any)) {
+                uint32_t n0 = ex0[j], n1 = ex1[j];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((b & ((1u << c) - 1u)) == 0u) count_request((sr[j] >> (8 * c)) & 7u, n0, n1);
+                L.run_end[sub][0] = any == 0ull ? 0u : 1u;
+                L.run_end[sub][1] = n0;
+                L.run_end[sub][2] = n1;
+            }
+        }
+    }
+
     // ---- 3. one wave: first slots per sub-block, queue starts, stage costs, downstream maxima ----
     if (wave == 0) {
         // lane i < SUB takes sub-block i; exclusive prefix over the sub-blocks per stage
@@ -230,7 +365,7 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
             *reinterpret_cast<uint4*>(&L.first_slot[lane][0]) = v;
         }
         if (lane == 0) L.verdict = disorder ? 1u : 0u;
-        if (!disorder) {
+        if (!disorder && !RANKED) {
             // downstream maximum per stage over the path CSR (or as given); only this wave is involved
             __builtin_amdgcn_s_waitcnt(0);
             __builtin_amdgcn_wave_barrier();
@@ -314,6 +449,13 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     }
 
     // ---- 4. queue slot, estimate, drop decision -------------------------------------------------
+    uint32_t topo[RANKED ? kPsStages : 1];   // ranked, by place (successors have lower places): stage | successors' places << 16
+    uint32_t with_end = 0;                   // ranked: the sub-blocks in which a run of equal deadlines ends
+    if constexpr (RANKED) {
+#pragma unroll
+        for (int p = 0; p < kPsStages; ++p) topo[p] = (uint32_t)__builtin_amdgcn_readfirstlane(p < S ? (int)P.topo[((int64_t)dag * S + p) * 2] : 0);
+        with_end = (uint32_t)__ballot(lane < SUB && L.run_end[lane < SUB ? lane : 0][0] != 0u);
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int base = wbase + j * 256;
@@ -323,11 +465,18 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
         int32_t est[4];
         uint8_t drp[4];
         asm volatile("" ::: "memory");       // one sub-block at a time (register pressure)
+        uint32_t e32[4] = {0, 0, 0, 0};
+        if constexpr (RANKED) ranked_estimates<T>(L, S, wave * 4 + j, lane, sr[j], ex0[j], ex1[j], (ends >> (4 * j)) & 15u, with_end, topo, e32);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const uint32_t k = (sr[j] >> (8 * c)) & 7u;     // slots that are not live compute on the zeroed rows of stage 7 and are discarded
             const uint32_t slot = CONS ? (place[CONS ? 2 * j + (c >> 1) : 0] >> (16 * (c & 1))) & 0xFFFFu
                                        : (uint32_t)fs[k] + ((uint32_t)(before >> (k * 10u)) & 1023u) + ((sr[j] >> (8 * c + 3)) & 7u);
+            if constexpr (RANKED) {
+                finish_request(e32[c], now, dl[j][c], est[c], drp[c]);
+                if (live(base + c)) L.ord[slot] = (uint16_t)(base + c);
+                continue;
+            }
             const uint32_t decided = CONS ? L.chain[live(base + c) ? slot : 0u] : 0u;
             const uint4 qa = *reinterpret_cast<const uint4*>(&L.quick[k][0]);     // B-1, 1/B, 1/W, aW
             const uint4 qb = *reinterpret_cast<const uint4*>(&L.quick[k][4]);     // bW, queue start, downstream
@@ -443,10 +592,12 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
 #ifndef PARD_PS_WAVES
 #define PARD_PS_WAVES 6
 #endif
-template <int T, bool CONS>
-__global__ __launch_bounds__(T, PARD_PS_WAVES) void presorted_snapshot_kernel(FusedArgs A) {
+// Ranked: four (128 registers).  Six would spill a hundred of them (4096 snapshots of 8192: 534 us for the call and the compaction,
+// 289 with four).
+template <int T, bool CONS, bool RANKED>
+__global__ __launch_bounds__(T, RANKED ? 4 : PARD_PS_WAVES) void presorted_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = 16 * T;
-    __shared__ PresortedLds<T, CONS> L;
+    __shared__ PresortedLds<T, CONS, RANKED> L;
     const int u = blockIdx.x;
     const int64_t n = A.n;
     // snapshot bounds, made safe whatever snap_ptr holds
@@ -481,8 +632,8 @@ __global__ __launch_bounds__(T, PARD_PS_WAVES) void presorted_snapshot_kernel(Fu
     const int shift = (int)(lo & 3);
     const bool aligned = (bits & 15) == 0 && m + shift <= kCap;
     const int off = aligned ? shift : 0;
-    if (m == kCap && aligned && off == 0) presorted_body<T, true, CONS>(A, L, u, lo, m, true, 0);
-    else presorted_body<T, false, CONS>(A, L, u, lo, m, aligned, off);
+    if (m == kCap && aligned && off == 0) presorted_body<T, true, CONS, RANKED>(A, L, u, lo, m, true, 0);
+    else presorted_body<T, false, CONS, RANKED>(A, L, u, lo, m, aligned, off);
 }
 
 }  // namespace
@@ -503,11 +654,16 @@ bool presorted_path_covers(const FusedArgs& a) {
 
 hipError_t launch_presorted(const FusedArgs& a, hipStream_t stream) {
     const dim3 grid((unsigned)a.plan.K);
-    if (a.consistent) presorted_snapshot_kernel<512, true><<<grid, dim3(512), 0, stream>>>(a);
-    else if (a.cap <= 1024) presorted_snapshot_kernel<64, false><<<grid, dim3(64), 0, stream>>>(a);
-    else if (a.cap <= 2048) presorted_snapshot_kernel<128, false><<<grid, dim3(128), 0, stream>>>(a);
-    else if (a.cap <= 4096) presorted_snapshot_kernel<256, false><<<grid, dim3(256), 0, stream>>>(a);
-    else presorted_snapshot_kernel<512, false><<<grid, dim3(512), 0, stream>>>(a);
+    auto by_capacity = [&](auto ranked) {
+        constexpr bool R = decltype(ranked)::value;
+        if (a.cap <= 1024) presorted_snapshot_kernel<64, false, R><<<grid, dim3(64), 0, stream>>>(a);
+        else if (a.cap <= 2048) presorted_snapshot_kernel<128, false, R><<<grid, dim3(128), 0, stream>>>(a);
+        else if (a.cap <= 4096) presorted_snapshot_kernel<256, false, R><<<grid, dim3(256), 0, stream>>>(a);
+        else presorted_snapshot_kernel<512, false, R><<<grid, dim3(512), 0, stream>>>(a);
+    };
+    if (a.consistent) presorted_snapshot_kernel<512, true, false><<<grid, dim3(512), 0, stream>>>(a);
+    else if (a.ranked) by_capacity(std::true_type{});
+    else by_capacity(std::false_type{});
     return hipGetLastError();
 }
 

@@ -184,10 +184,10 @@ __global__ __launch_bounds__(kRSnapThreads) void ranked_snapshot_kernel(RankedAr
 // hands them to all.  The maximum over the paths is formed stage by stage (places rise away from the sinks) instead of
 // path by path.  A search starts from a table per queue of where every 2^shift-th deadline value of the snapshot's range
 // begins: one or two LDS steps are left of the binary search's eleven.  The table costs two bytes per bucket, a bucket
-// holds about one slot of a queue.  Saturating 32-bit sums are enough: 2^32 - 1 and everything above it is past INT32_MAX
+// holds about one slot of a queue.  Snapshots in queue order don't come here where pard_presorted.hip takes them.  Saturating 32-bit sums are enough: 2^32 - 1 and everything above it is past INT32_MAX
 // as an estimate and past every deadline that can be exceeded, even from the lowest `now`.  Bound by vector instructions
 // and dependent LDS
-// reads (about 230 and 24 per 64 slots at 6 stages).  4096 snapshots of 8192: 345 us, 967 with a binary search over the
+// reads (about 230 and 24 per 64 slots at 6 stages).  4096 snapshots of 8192 (high budget first): 345 us, 967 with a binary search over the
 // whole queue and a walk of the paths per request (more than 16 stages still take that: ranked_snapshot_kernel).
 __device__ __forceinline__ uint32_t sat32(uint64_t c) { return c < 0xFFFFFFFFull ? (uint32_t)c : 0xFFFFFFFFu; }
 __device__ __forceinline__ int from_lane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
@@ -205,9 +205,10 @@ __global__ __launch_bounds__(T) void ranked_queues_kernel(RankedArgs A, int cap,
     const int S = P.S, buckets = 1 << bucket_bits;
     uint16_t* table = reinterpret_cast<uint16_t*>(dls + cap);
     const int32_t u = blockIdx.x;
+    const uint32_t marked = A.todo ? A.todo[u] : 1u;    // 0: came in queue order, its estimates are the ranked ones already
     const int64_t a0 = A.seg_ptr[(int64_t)u * S], a1 = A.seg_ptr[(int64_t)(u + 1) * S];
     if (a0 < 0 || a1 < a0 || a1 > A.n || a1 - a0 > A.max_snapshot) return;   // larger than promised: reported by the plain call
-    if (a1 == a0) return;
+    if (a1 == a0 || marked == 0u) return;
     const int64_t rec0 = P.shared ? 0 : (int64_t)u * S;
     // lane i: where queue i starts (lane S: the end); lane p: the stage at place p, its queue's start and length, its order
     const int at = (int)((int64_t)A.seg_ptr[(int64_t)u * S + (lane < S ? lane : S)] - a0);

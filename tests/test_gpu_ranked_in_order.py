@@ -1,0 +1,74 @@
+"""Ranked positions of snapshots that come in queue order, formed by the kernel for queue order: runs of equal deadlines inside a
+lane's four requests, over lanes, over blocks of 256 and to the end of a snapshot, at the edges of the capacities and off 16-byte
+boundaries; marked and unmarked snapshots in one batch."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2602_08747_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+I32 = np.iinfo(np.int32)
+
+
+def in_order(seed, sizes, S, runs, shuffle=()):
+    """Snapshots of the given sizes in deadline order; a deadline is shared by about `runs` neighbours (0: by all)."""
+    K = len(sizes)
+    w = wl.random_workload(seed, K=K, S=S, n_per_snapshot=4, modes=(wl.MODE_LBF,))
+    rng = np.random.default_rng([seed, 5])
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(ptr[-1])
+    deadline = np.empty(n, np.int64)
+    for u in range(K):
+        m = sizes[u]
+        steps = rng.random(m) < (1.0 / runs if runs else 0.0)
+        deadline[ptr[u]:ptr[u + 1]] = 20000 + np.cumsum(steps * rng.integers(1, 40, m))
+        if u in shuffle:
+            rng.shuffle(deadline[ptr[u]:ptr[u + 1]])
+    return dataclasses.replace(w, arrival=np.zeros(n, np.int32), deadline=deadline.astype(np.int32),
+                               stage=rng.integers(0, S, n).astype(np.int32), snap_ptr=ptr, now=rng.integers(0, 30000, K).astype(np.int32))
+
+
+def wide(w):
+    d = w.deadline.copy()
+    for u in range(w.K):
+        lo, hi = w.snap_ptr[u], w.snap_ptr[u + 1]
+        d[lo:hi][: max(1, (hi - lo) // 3)] = I32.min
+        d[lo:hi][-max(1, (hi - lo) // 4):] = I32.max
+    return dataclasses.replace(w, deadline=d)
+
+
+EDGES = {"1024": [513, 1023, 1024, 1, 0, 700] * 3, "2048": [2048, 1025, 2045, 3] * 3, "4096": [4096, 4095, 2049] * 2,
+         "8192": [8192, 4097, 8189, 8191]}
+
+
+@pytest.mark.parametrize("S", [2, 3, 6])
+@pytest.mark.parametrize("runs", [0, 1, 2, 5, 90, 600])
+@pytest.mark.parametrize("edge", list(EDGES))
+def test_ranked_in_order(oracle_mod, edge, runs, S):
+    check(oracle_mod, in_order(100 * runs + S, EDGES[edge], S, runs))
+
+
+@pytest.mark.parametrize("which", ["wide", "some-shuffled", "many-small"])
+def test_ranked_in_order_mixed(oracle_mod, which):
+    if which == "wide":
+        w = wide(in_order(1, [3000, 8192, 5001], 5, 3))
+    elif which == "some-shuffled":
+        w = in_order(2, [2500, 4096, 3333, 4001], 4, 2, shuffle=(1, 3))
+    else:
+        w = in_order(3, [600 + i for i in range(300)], 6, 4, shuffle=tuple(range(0, 300, 7)))
+    check(oracle_mod, w)
+
+
+def check(oracle_mod, w):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU and the built libpard.so")
+    from paper_2602_08747_amd import binding
+    ref = oracle_mod.run(w, threads=8, ranked=True)
+    s = binding.Session(w)
+    s.run(ranked=True)
+    got = s.results()
+    for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
+        assert np.array_equal(got[k], ref[k]), k
