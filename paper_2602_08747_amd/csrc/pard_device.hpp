@@ -141,9 +141,8 @@ __device__ __forceinline__ int32_t wave_exclusive_min(int32_t v) {
 // Behind the first batch the cost is floor(q lat[B] / W) + lat[B] with q = ceil(pos / B), so q < (budget - lat[B] + 1) W / lat[B]:
 // a float quotient, off by less than 0.01, and one exact comparison to either side.  In the first batch the wait is that
 // of one batch and the execution one of B table entries.
-__device__ __forceinline__ uint32_t positions_in_time(const uint32_t* quick, float inv, const uint32_t* lat, int64_t budget) {
-    if (budget < (int64_t)lat[0]) return 0u;
-    const uint32_t b = budget < 0xFFFFFFFFll ? (uint32_t)budget : 0xFFFFFFFFu;      // every cost is below 2^32
+// positions_from: the same for a budget b of at least lat[0].
+__device__ __forceinline__ uint32_t positions_from(const uint32_t* quick, float inv, const uint32_t* lat, uint32_t b) {
     const uint4 qa = *reinterpret_cast<const uint4*>(quick);
     const uint32_t bW = quick[4];
     auto wait = [&](uint32_t q) { return __umul24(q, qa.w) + (uint32_t)(((float)__umul24(q, bW) + 0.5f) * __uint_as_float(qa.z)); };
@@ -162,6 +161,11 @@ __device__ __forceinline__ uint32_t positions_in_time(const uint32_t* quick, flo
     if (wait(q) > room) --q;
     else if (wait(q + 1u) <= room) ++q;
     return q * (qa.x + 1u) + 1u;
+}
+
+__device__ __forceinline__ uint32_t positions_in_time(const uint32_t* quick, float inv, const uint32_t* lat, int64_t budget) {
+    if (budget < (int64_t)lat[0]) return 0u;
+    return positions_from(quick, inv, lat, budget < 0xFFFFFFFFll ? (uint32_t)budget : 0xFFFFFFFFu);         // every cost is below 2^32
 }
 
 // One step of a queue's chain under low budget first: 64 requests in queue order (`ok` in the lanes that hold one), c = how

@@ -25,8 +25,8 @@
 //      earlier lanes + rank inside the lane; own-stage cost in the exact short-queue form,
 //      estimate, drop decision; outputs leave in request order, the queue order via LDS.
 //      Sequentially consistent variant (positions count the kept requests ahead): every thread first leaves, by queue
-//      slot, in how many positions its requests are in time, one wave per queue turns those into positions and decisions
-//      (a prefix minimum per 64 requests), and the estimates are formed from the positions.
+//      slot, in how many positions its requests are in time, one prefix minimum over the slots turns those into positions
+//      and decisions, and the estimates are formed from the positions.
 #include "pard_device.hpp"
 #include <type_traits>
 
@@ -68,8 +68,11 @@ struct PresortedLds {
     uint32_t disorder[T / kWave];                             // per wave: it saw a deadline fall
     uint32_t ktot[SUB];                                       // kept slots per sub-block
     uint32_t ent[kPsEntries];                                 // the DAG's path entries: stage | (end of the entry's path) << 8
-    uint16_t chain[CONS ? CAP : 1];                           // sequentially consistent, by queue slot: positions the request is in time
-                                                              // at, then its position | drop << 15
+    __align__(16) int32_t chain[CONS ? CAP : 4];              // sequentially consistent, by queue slot: positions the request is in time
+                                                              // at less its place in the queue, then the least of those ahead
+    int32_t chain_least[CONS ? T / kWave : 1];
+    int32_t due[8];                                           // sequentially consistent: now + downstream, at most INT32_MAX: nobody with a
+                                                              // deadline below it is in time (a deadline of INT32_MAX always is)
     float inv[8];                                             // sequentially consistent: W / lat[B] per stage
     uint32_t run_end[RANKED ? SUB : 1][3];                    // ranked: per sub-block, 1 where a run of equal deadlines ends in it, and the
                                                               // requests per stage up to the first such end (10-bit fields)
@@ -396,6 +399,10 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
                 const unsigned long long d = L.down[lane];
                 L.quick[lane][6] = (uint32_t)d;
                 L.quick[lane][7] = (uint32_t)(d >> 32);
+                if (CONS) {
+                    const int64_t due = (int64_t)now + (int64_t)d;          // d is at most 65 terms of 2^40
+                    L.due[lane] = due < (int64_t)kInt32Max ? (int32_t)due : kInt32Max;
+                }
             }
         }
     }
@@ -406,7 +413,12 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     }
     if (tid == 0) A.todo[u] = 0u;
 
-    // ---- sequentially consistent: positions in time by queue slot, then every queue's chain of decisions --------
+    // ---- sequentially consistent: positions in time by queue slot, then the chains of decisions of all queues --------
+    // With c positions in time a request is kept iff fewer are kept ahead of it.  Budgets rise along a queue, so does c, and the
+    // recurrence a' = min(a + 1, c) unrolls to a_i = min(i, i - 1 + min over i' < i of (c_i' - i')): an exclusive prefix
+    // minimum, here over all slots at once.  Queue k's values are lowered by k 2^16, more than they span, so what is left
+    // from an earlier queue is too high to matter.  (A wave per queue, 64 slots at a step: 4096 snapshots of 8192 in overload, with
+    // the compaction, 254 us, now 234; the scan is 10 of it.)
     uint32_t place[CONS ? 8 : 1];            // two queue slots per word
     if (CONS) {
 #pragma unroll
@@ -420,30 +432,49 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
                 const uint32_t k = (sr[j] >> (8 * c)) & 7u;
                 const uint32_t slot = (uint32_t)fs[k] + ((uint32_t)(before >> (k * 10u)) & 1023u) + ((sr[j] >> (8 * c + 3)) & 7u);
                 if (c & 1) place[2 * j + (c >> 1)] |= slot << 16; else place[2 * j + (c >> 1)] = slot;
+                uint32_t v = 0x7FFFu;
+                asm volatile("" ::: "memory");   // one request at a time
                 if (live(base + c)) {
-                    uint32_t v = 0x7FFFu;
                     if (dl[j][c] != kInt32Max) {
-                        const uint64_t dn = (uint64_t)L.quick[k][6] | ((uint64_t)L.quick[k][7] << 32);
-                        v = positions_in_time(&L.quick[k][0], L.inv[k], &L.lat[k * PARD_LAT_ENTRIES], (int64_t)dl[j][c] - (int64_t)now - (int64_t)dn);
+                        const int32_t due = L.due[k];
+                        const uint32_t left = (uint32_t)dl[j][c] - (uint32_t)due, *lat = &L.lat[k * PARD_LAT_ENTRIES];
+                        v = dl[j][c] < due || left < lat[0] ? 0u : positions_from(&L.quick[k][0], L.inv[k], lat, left);
+                        v = v < 0x7FFFu ? v : 0x7FFFu;
                     }
-                    L.chain[slot] = (uint16_t)(v < 0x7FFFu ? v : 0x7FFFu);
+                    L.chain[slot] = (int32_t)v - (int32_t)(slot - L.quick[k][5]) - (int32_t)(k << 16);
                 }
+                dl[j][c] = (int32_t)v;           // (the deadline has done its part)
             }
+            if constexpr (CONS) asm volatile("" : "+v"(place[2 * j]), "+v"(place[2 * j + 1]), "+v"(dl[j][0]), "+v"(dl[j][1]), "+v"(dl[j][2]), "+v"(dl[j][3]));
         }
         __syncthreads();
-        for (int k = wave; k < S; k += T / kWave) {            // one wave per queue
-            const int s0 = L.seg_start[k], s1 = L.seg_start[k + 1];
-            uint32_t kept = 0;
-            uint32_t next = s0 + lane < s1 ? L.chain[s0 + lane] : 0u;
-            for (int first = s0; first < s1; first += kWave) {
-                const int at = first + lane;
-                const int c = (int)next - (int)kept;
-                next = at + kWave < s1 ? L.chain[at + kWave] : 0u;
-                unsigned long long keep;
-                const int a = chain_step(at < s1, c, lane, keep);
-                if (at < s1) L.chain[at] = (uint16_t)((kept + (uint32_t)a) | (a < c ? 0u : 0x8000u));
-                kept += (uint32_t)__popcll(keep);
+        // lane l of wave w: slots 1024 w + 256 j + 4 l + c (behind the last request: anything, and nothing follows them)
+        int32_t v[4][4], ahead[4], wave_least = 1 << 30;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int4 x = *reinterpret_cast<const int4*>(&L.chain[wbase + j * 256]);
+            v[j][0] = x.x; v[j][1] = x.y; v[j][2] = x.z; v[j][3] = x.w;
+            const int32_t a = x.x < x.y ? x.x : x.y, b = x.z < x.w ? x.z : x.w, mine = a < b ? a : b;
+            const int32_t below = wave_exclusive_min(mine);
+            ahead[j] = below < wave_least ? below : wave_least;
+            const int32_t all = __builtin_amdgcn_readlane(below < mine ? below : mine, kWave - 1);
+            wave_least = all < wave_least ? all : wave_least;
+        }
+        if (lane == 0) L.chain_least[wave] = wave_least;
+        __syncthreads();
+        int32_t before = 1 << 30;
+#pragma unroll
+        for (int w = 0; w < T / kWave - 1; ++w)
+            if (w < wave) before = L.chain_least[w] < before ? L.chain_least[w] : before;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            int32_t run = ahead[j] < before ? ahead[j] : before, out[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                out[c] = run;
+                run = v[j][c] < run ? v[j][c] : run;
             }
+            *reinterpret_cast<int4*>(&L.chain[wbase + j * 256]) = make_int4(out[0], out[1], out[2], out[3]);
         }
         __syncthreads();
     }
@@ -477,10 +508,13 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
                 if (live(base + c)) L.ord[slot] = (uint16_t)(base + c);
                 continue;
             }
-            const uint32_t decided = CONS ? L.chain[live(base + c) ? slot : 0u] : 0u;
             const uint4 qa = *reinterpret_cast<const uint4*>(&L.quick[k][0]);     // B-1, 1/B, 1/W, aW
             const uint4 qb = *reinterpret_cast<const uint4*>(&L.quick[k][4]);     // bW, queue start, downstream
-            const uint32_t pos = CONS ? decided & 0x7FFFu : slot - qb.y;
+            uint32_t pos = slot - qb.y;
+            if (CONS) {
+                const int32_t i = (int32_t)pos, bound = i - 1 + L.chain[live(base + c) ? slot : 0u] + (int32_t)(k << 16);
+                pos = (uint32_t)(bound < i ? bound : i);
+            }
             const uint32_t q = (uint32_t)(((float)(pos + qa.x) + 0.5f) * __uint_as_float(qa.y));
             const uint32_t p = __umul24(q, qb.x);
             const uint32_t wait = __umul24(q, qa.w) + (uint32_t)(((float)p + 0.5f) * __uint_as_float(qa.z));
@@ -489,7 +523,7 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
             const uint64_t e64 = (uint64_t)wait + L.lat[k * PARD_LAT_ENTRIES + seen] + dn;
             if (CONS) {
                 est[c] = e64 > (uint64_t)kInt32Max ? kInt32Max : (int32_t)e64;
-                drp[c] = (uint8_t)(decided >> 15);
+                drp[c] = pos < (uint32_t)dl[j][c] ? 0 : 1;
             } else {
                 finish_request(e64, now, dl[j][c], est[c], drp[c]);
             }
