@@ -251,7 +251,7 @@ static int estimate_drop_impl(const pard_plan_t* plan, int64_t n, int64_t max_sn
         a.num_cus = plan->num_cus;
         if (ranked_todo && plan->host.S > 1) {       // (one stage: the plain estimates are the ranked ones)
             a.ranked = 1;
-            if (tries_queue_order(a)) *ranked_todo = a.todo;
+            if (ranked_in_queue_order(a)) *ranked_todo = a.todo;
         }
         e = launch_fused(a, s);
     } else {

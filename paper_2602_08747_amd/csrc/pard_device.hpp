@@ -214,14 +214,15 @@ struct FusedArgs {
     int32_t* loc_ptr;                  // [K*S] out: survivors of the snapshot before each of its queues
     int32_t cap;                       // promised bound on a snapshot's size
     int32_t consistent;                // positions count only the kept requests ahead
-    int32_t ranked;                    // launch_ranked follows: the kernel for queue order forms the ranked estimates of what it finishes,
-                                       // the general one only the queues
+    int32_t ranked;                    // launch_ranked follows: the general kernel forms only the queues, the one for queue order the
+                                       // ranked estimates of what it finishes where ranked_in_queue_order says so
     int64_t n;                         // total requests (bounds every index derived from snap_ptr)
     int32_t num_cus;
 };
 hipError_t launch_fused(const FusedArgs& a, hipStream_t stream);
-// Whether launch_fused lets the kernel for queue order try first (todo[] then says which snapshots it left).
-bool tries_queue_order(const FusedArgs& a);
+// Ranked calls: whether the kernel for queue order tries first and finishes what it takes (todo[] then says which snapshots
+// launch_ranked still has to do; else it does all of them).
+bool ranked_in_queue_order(const FusedArgs& a);
 // Snapshots whose requests already come in queue order (launch_fused tries this first when it applies).
 constexpr int kPresortedMaxStages = 6;
 bool presorted_path_covers(const FusedArgs& a);

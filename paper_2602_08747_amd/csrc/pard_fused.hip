@@ -795,12 +795,28 @@ void launch_capacity(const FusedArgs& a, hipStream_t stream) {
 namespace {
 int wide_threads(int32_t cap) { return cap <= 512 ? 128 : cap <= 1024 ? 256 : cap <= 2048 ? 512 : 1024; }
 bool few_snapshots(const FusedArgs& a) { return a.cap > 256 && (int64_t)a.plan.K * wide_threads(a.cap) <= 1024 * (int64_t)a.num_cus; }
-}  // namespace
 
+// Whether the kernel for queue order goes first (the rule's figures are in launch_fused).
 bool tries_queue_order(const FusedArgs& a) {
     if (wave_path_covers(a)) return false;
     const bool alone = few_snapshots(a) && (a.consistent ? a.n <= 3072 * (int64_t)a.plan.K : a.cap <= 4096 && a.n <= 8192);
     return !alone && presorted_path_covers(a);
+}
+}  // namespace
+
+// The kernel for queue order gives a wave 1024 neighbouring requests, so under a loose bound a few waves of a workgroup do
+// all of a snapshot's ranked estimates, at more registers than its plain form, while ranked_queues_kernel spreads the slots
+// over all of its waves.  Snapshots in order, six stages, with the compaction, the plain form and ranked_queues_kernel / the
+// ranked form: 6000 of 2100 under 8192 330 / 355 us, 2500 355 / 359, 2800 353 / 343, 3200 377 / 347; 12,000 of 700 478 / 570;
+// 8000 under 4096 of 1000 238 / 251, 1300 256 / 261, 1500 265 / 262, 1700 279 / 269; two stages cross lower (2100 under 8192
+// 260 / 269, 2800 270 / 259; 1300 under 4096 211 / 198).  Hence a third.  Workgroups of one and two waves always gain (300 under 1024 193 /
+// 158, 100 under 2048 136 / 114, 600 181 / 177).  Few snapshots run at once and cross earlier: 200 under 8192 of 1000 34.3 / 35.4, of 1500
+// 36.7 / 35.5, of 2500 43.7 / 37.1; 200 of 1000 under 4096 33.4 / 34.7.
+bool ranked_in_queue_order(const FusedArgs& a) {
+    if (!a.ranked || !tries_queue_order(a)) return false;
+    if (a.cap <= 2048) return true;
+    const int64_t capacity = a.cap <= 4096 ? 4096 : PARD_FUSED_SNAPSHOT_CAPACITY;
+    return a.n > (int64_t)a.plan.K * (few_snapshots(a) ? 1024 : capacity / 3);
 }
 
 hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {

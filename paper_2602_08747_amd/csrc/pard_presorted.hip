@@ -201,7 +201,7 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     const PlanDev& P = A.plan;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
+    const int wave = RANKED ? __builtin_amdgcn_readfirstlane(tid / kWave) : tid / kWave;
     const int S = P.S;
     const int dag = P.shared ? 0 : u;
     const int32_t* lat_dag = P.lat + (int64_t)dag * S * PARD_LAT_ENTRIES;
@@ -297,14 +297,23 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
 
     // ---- ranked: where the runs of equal deadlines end ---------------------------------------
     uint32_t ends = 0;                      // bit 4 j + c: the next request's deadline is another one
+    // The last request ends its run, and so does every slot behind it: sub-blocks that lie there are left out altogether.
+    // (With the compaction, their estimates formed and thrown away / left out: 12,000 snapshots of 1500 through the largest
+    // workgroup 915 / 658 us, 3000 of up to 8000 258 / 224, 12,000 of up to 1000 151 / 133, 4096 full ones 290 / 285.)
+    auto past_end = [&](int sub) { return !FULL && sub * 256 >= m_s; };
+    auto behind_last = [&](int base) -> uint32_t { return FULL || base + 4 < m_s ? 0u : 15u & (15u << (m_s - 1 > base ? m_s - 1 - base : 0)); };
     if (RANKED) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int sub = wave * 4 + j;
+            if (past_end(sub)) {
+                if (lane == 0) L.run_end[sub][0] = 0u;
+                continue;
+            }
             int32_t after = __builtin_amdgcn_update_dpp(0, dl[j][0], 0x130, 0xF, 0xF, false);       // wave_shl:1, the next lane's first
             if (lane == kWave - 1) after = sub + 1 < SUB ? L.edge_lo[sub + 1] : ~dl[j][3];          // nothing lies behind the last
             const uint32_t b = (dl[j][0] != dl[j][1] ? 1u : 0u) | (dl[j][1] != dl[j][2] ? 2u : 0u) |
-                               (dl[j][2] != dl[j][3] ? 4u : 0u) | (dl[j][3] != after ? 8u : 0u);
+                               (dl[j][2] != dl[j][3] ? 4u : 0u) | (dl[j][3] != after ? 8u : 0u) | behind_last(wbase + j * 256);
             ends |= b << (4 * j);
             const unsigned long long any = __ballot(b != 0u);
             if (any == 0ull ? lane == 0 : lane == __builtin_ctzll(any)) {
@@ -489,6 +498,7 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+        if (RANKED && past_end(wave * 4 + j)) continue;
         const int base = wbase + j * 256;
         // requests of every stage in earlier lanes of this sub-block: six 10-bit fields of a 64-bit word
         const unsigned long long before = (unsigned long long)ex0[j] | ((unsigned long long)ex1[j] << 30);
@@ -696,7 +706,7 @@ hipError_t launch_presorted(const FusedArgs& a, hipStream_t stream) {
         else presorted_snapshot_kernel<512, false, R><<<grid, dim3(512), 0, stream>>>(a);
     };
     if (a.consistent) presorted_snapshot_kernel<512, true, false><<<grid, dim3(512), 0, stream>>>(a);
-    else if (a.ranked) by_capacity(std::true_type{});
+    else if (ranked_in_queue_order(a)) by_capacity(std::true_type{});
     else by_capacity(std::false_type{});
     return hipGetLastError();
 }

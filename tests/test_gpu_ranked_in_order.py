@@ -1,6 +1,6 @@
 """Ranked positions of snapshots that come in queue order, formed by the kernel for queue order: runs of equal deadlines inside a
 lane's four requests, over lanes, over blocks of 256 and to the end of a snapshot, at the edges of the capacities and off 16-byte
-boundaries; marked and unmarked snapshots in one batch."""
+boundaries; marked and unmarked snapshots in one batch; snapshots that end anywhere in a workgroup laid out for a larger bound."""
 import dataclasses
 
 import numpy as np
@@ -61,14 +61,40 @@ def test_ranked_in_order_mixed(oracle_mod, which):
     check(oracle_mod, w)
 
 
-def check(oracle_mod, w):
+ENDS = [255, 256, 257, 1, 0, 3, 511, 513, 767, 1023, 1025, 1279, 1793]
+
+
+@pytest.mark.parametrize("S", [2, 5])
+@pytest.mark.parametrize("runs", [0, 1, 3, 200])
+@pytest.mark.parametrize("sizes,bound", [(ENDS, 2048), (ENDS, 4096), (ENDS, 8192), ([2049, 2047, 1021, 3071], 8192), ([1024] * 9, 4096),
+                                         ([1025] * 9, 8192), ([1365] * 260, 4096), ([1366] * 260, 4096), ([2730] * 260, 8192), ([2731] * 259 + [2732], 8192)])
+def test_loose_bound(oracle_mod, sizes, bound, runs, S):
+    """A bound far above the sizes, on both sides of the mean size from which the in-order kernel forms the ranked estimates itself
+    (1024 of few snapshots, a third of the workgroup's capacity of many, where that is 4096 or 8192)."""
+    times = 1 if len(sizes) > 100 else -(-8300 // sum(sizes))          # (calls of at most 8192 requests don't come here)
+    w = in_order(1000 * runs + S + bound, sizes * times, S, runs)
+    if runs != 1:
+        w = wide(w)
+    check(oracle_mod, w, bound)
+
+
+def check(oracle_mod, w, bound=None):
+    """Against the oracle, and the marks behind the workspace's 256-byte header: 0 where the in-order kernel took a snapshot."""
     import torch
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a GPU and the built libpard.so")
     from paper_2602_08747_amd import binding
     ref = oracle_mod.run(w, threads=8, ranked=True)
-    s = binding.Session(w)
-    s.run(ranked=True)
+    s = binding.Session(w, max_snapshot_requests=bound)
+    s.workspace[64:64 + w.K] = -5
+    s.est.fill_(-3)
+    s.drop.fill_(7)
+    s.estimate_drop(ranked=True)
+    marks = s.workspace[64:64 + w.K].cpu().numpy()
+    falls = [bool((np.diff(w.deadline[w.snap_ptr[u]:w.snap_ptr[u + 1]].astype(np.int64)) < 0).any()) for u in range(w.K)]
+    assert np.array_equal(marks, np.array(falls, np.int32))
+    s.compact()
     got = s.results()
     for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
         assert np.array_equal(got[k], ref[k]), k
+    assert s.status_word() == 0
