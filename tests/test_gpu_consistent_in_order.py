@@ -207,3 +207,44 @@ def test_positions_in_time_at_every_step(oracle_mod, most, least, shuffled):
     for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
         assert np.array_equal(got[k], ref[k]), k
     assert (s.workspace[64:64 + w.K].cpu().numpy() == (-5 if most >= 1 << 17 else int(shuffled))).all()
+
+
+DUE = [(-2**31, 0), (-2**31, 2**32 - 2), (-2**31, 2**32 - 1), (-2**31, 2**32), (-2**31, 2**40), (-2**31, 2**31 + 77), (-1000, 3), (0, 2**31 - 2), (0, 2**31 - 1),
+       (7, 2**31 - 7), (2**31 - 1, 0), (2**31 - 1, 1), (2**31 - 1, 2**40), (12345, 999_999)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("first", [0, 1, 900])             # the cost of the first position
+def test_due_time_at_the_ends(oracle_mod, first):
+    """`now` plus the downstream latency up to, at and past INT32_MAX, and deadlines at both ends of their range and a microsecond
+    around that sum and the first costs: the kernel for queue order compares the two in 32 bits."""
+    import torch
+    from paper_2602_08747_amd import binding
+    K, S, per = len(DUE), 2, 8000
+    rng = np.random.default_rng(first)
+    lat = first + 3 * np.arange(64)
+    row_ptr, col = wl.csr_from_edges(S, wl.chain_edges(S))
+    deadline = np.empty((K, per), np.int64)
+    for u, (now, down) in enumerate(DUE):
+        due = now + down
+        near = due + np.concatenate([np.arange(-2, 3), first + np.arange(-2, 3), first + 3 + np.arange(-2, 3), [-2**31, -50]])
+        span = int(cost(5000, 4, 2, lat))                  # as long as the queue keeps up with the positions in time
+        deadline[u] = np.concatenate([np.repeat(near, 20), np.repeat([-2**31, 2**31 - 2, 2**31 - 1], 50), due + rng.integers(-span // 8, span, per)])[:per]
+    deadline = np.sort(np.clip(deadline, -2**31, 2**31 - 1), axis=1)
+    n = K * per
+    w = wl.Workload(name="due", K=K, S=S, dag_shared=1, dag_row_ptr=row_ptr, dag_col=col, batch=np.full(S, 4, np.int32), workers=np.full(S, 2, np.int32),
+                    lat_us=np.tile(lat, S).astype(np.int32), order_mode=np.full(S, wl.MODE_LBF, np.int32), arrival=np.zeros(n, np.int32),
+                    deadline=np.ascontiguousarray(deadline.reshape(-1), np.int32), stage=rng.integers(0, S, n).astype(np.int32),
+                    snap_ptr=(np.arange(K + 1) * per).astype(np.int32), now=np.array([d[0] for d in DUE], np.int32))
+    sub = np.repeat(np.array([d[1] for d in DUE], np.int64), S)
+    ref = oracle_mod.run(w, threads=8, sub=sub, consistent=True)
+    late = np.repeat(np.array([sum(d) >= 2**31 - 1 for d in DUE]), per)
+    kept = w.deadline == 2**31 - 1
+    assert (ref["drop"][late & ~kept] == 1).mean() > 0.99 and (ref["drop"][kept] == 0).all() and 0.1 < ref["drop"][~late].mean() < 0.9
+    s = binding.Session(w)
+    s.workspace[64:64 + K] = -5
+    s.run(sub=torch.from_numpy(sub).to(s.dev), consistent=True)
+    got = s.results()
+    for k in ("est", "drop", "order", "seg_ptr", "surv_idx", "surv_ptr"):
+        assert np.array_equal(got[k], ref[k]), k
+    assert (s.workspace[64:64 + K].cpu().numpy() == 0).all()

@@ -95,3 +95,38 @@ def test_larger_than_promised(K, most, size):
     lo = int(w.snap_ptr[2])
     if K > 2:
         assert np.array_equal(s.est.cpu().numpy()[lo:], good["est"][lo:]) and np.array_equal(s.drop.cpu().numpy()[lo:], good["drop"][lo:])
+
+
+@pytest.mark.parametrize("times", [1, 130])                # wide workgroups, and the usual ones
+@pytest.mark.parametrize("most,size", [(300, 307), (1000, 1013), (1500, 1700), (3000, 4001), (5000, 6000)])
+@pytest.mark.parametrize("kind", ["in-order", "low", "high"])
+def test_ranked_larger_than_promised(oracle_mod, most, size, kind, times):
+    """Ranked calls leave the plain estimates to no one else: a snapshot larger than promised still gets those of its first requests, the
+    last one, whose queues end where the promise does, the ranked ones, and the others are right."""
+    import torch
+    from paper_2602_08747_amd import binding
+    sizes = [most, size, most - 7] * times + [size]
+    K, lasts = len(sizes), len(sizes) - 1
+    w = wl.random_workload(most, K=K, S=3, n_per_snapshot=size, time_span=20 * most, slo_choices=(4 * most,) if kind == "in-order" else (3 * most, 6 * most),
+                           modes=(wl.MODE_HBF,) if kind == "high" else (wl.MODE_LBF,), dag_shared=1, vary_sizes=False)
+    row_ptr, col = wl.csr_from_edges(3, wl.chain_edges(3))
+    w = dataclasses.replace(w, dag_row_ptr=row_ptr, dag_col=col, lat_us=np.maximum(1, w.lat_us // 20).astype(np.int32))
+    w = wl.with_snapshot_sizes(w, sizes)
+    if kind == "in-order":
+        w = wl.in_deadline_order(w)
+    served = wl.with_snapshot_sizes(w, np.minimum(sizes, most))
+    plain, ranked = oracle_mod.run(served, threads=8), oracle_mod.run(served, threads=8, ranked=True)
+    assert not np.array_equal(plain["est"], ranked["est"])
+    s = binding.Session(w, max_snapshot_requests=most)
+    s.est.fill_(-3)
+    s.drop.fill_(7)
+    s.estimate_drop(ranked=True)
+    torch.cuda.synchronize()
+    assert s.status_word() == 1
+    est, drop = s.est.cpu().numpy(), s.drop.cpu().numpy()
+    for u in range(K):
+        a, b = int(w.snap_ptr[u]), int(served.snap_ptr[u])
+        m = min(sizes[u], most)
+        want = plain if sizes[u] > most and u != lasts else ranked
+        assert np.array_equal(est[a:a + m], want["est"][b:b + m]) and np.array_equal(drop[a:a + m], want["drop"][b:b + m]), u
+        assert (est[a + m:a + sizes[u]] == -3).all() and (drop[a + m:a + sizes[u]] == 7).all()

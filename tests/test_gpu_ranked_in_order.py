@@ -78,6 +78,36 @@ def test_loose_bound(oracle_mod, sizes, bound, runs, S):
     check(oracle_mod, w, bound)
 
 
+@pytest.mark.parametrize("S", [2, 3, 4, 6])
+@pytest.mark.parametrize("B,W,quotient", [(1, 256, (1 << 17) - 1), (1, 1, 1 << 16), (2, 255, (1 << 17) - 1), (64, 256, (1 << 17) - 1)])
+def test_sums_past_32_bits(oracle_mod, B, W, quotient, S):
+    """A chain whose first queue holds nearly all requests, its waits at the top of the short form (8000 batches near 2^30), and whose later stages take
+    up to 2^31 - 1 for a batch that is not full: along the first queue the sums cross 2^32 (INT32_MAX with one later stage)."""
+    sizes = [8192, 6001, 8000, 2049]
+    rng = np.random.default_rng([B, W, S])
+    w = in_order(S, sizes, S, 3)
+    row_ptr, col = wl.csr_from_edges(S, wl.chain_edges(S))
+    batch, workers = np.full(S, 64, np.int32), np.full(S, 3, np.int32)
+    batch[0], workers[0] = B, W
+    full = W * quotient + W - 1
+    lat = np.full((S, 64), 1000, np.int64)                # (a full batch of the later stages; the table falls)
+    lat[0] = full - (np.maximum(B - 1 - np.arange(64), 0) * full) // 100
+    whole = (1 << 32 if S > 2 else 1 << 31) - 4000 // B * quotient
+    lat[1:, :63] = whole // (S - 1)
+    stage, d = [], []
+    for m in sizes:
+        k = np.zeros(m, np.int32)
+        k[rng.permutation(m)[:40 * (S - 1)]] = np.repeat(np.arange(1, S), 40)
+        stage.append(k)
+        d.append(np.sort(rng.integers(I32.min, I32.max, m, endpoint=True)))
+    d[0][:400], d[0][-300:] = I32.min, I32.max
+    w = dataclasses.replace(w, dag_shared=1, dag_row_ptr=row_ptr, dag_col=col, batch=batch, workers=workers,
+                            lat_us=np.ascontiguousarray(lat.reshape(-1), np.int32), order_mode=np.full(S, wl.MODE_LBF, np.int32),
+                            deadline=np.concatenate(d).astype(np.int32), stage=np.concatenate(stage), now=np.array([I32.min, 0, I32.max, I32.min], np.int32))
+    assert lat.max() <= I32.max and full // W < 1 << 17
+    check(oracle_mod, w)
+
+
 def check(oracle_mod, w, bound=None):
     """Against the oracle, and the marks behind the workspace's 256-byte header: 0 where the in-order kernel took a snapshot."""
     import torch
