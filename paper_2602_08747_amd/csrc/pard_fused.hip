@@ -14,8 +14,11 @@
 //      drop decision; outputs leave in request order, the queue order via LDS.
 //      Sequentially consistent variant: the position counts only the requests ahead that
 //      were kept (the Request Broker takes a queue in order and a dropped request never
-//      takes a batch slot, Section 4.1), so a queue is a chain of decisions; one wave walks
-//      it 64 requests at a time and settles each group by iterating to the fixed point.
+//      takes a batch slot, Section 4.1), so a queue is a chain of decisions.  Long low-budget-
+//      first queues of the largest capacity: every request's number of positions in time, then
+//      one prefix minimum over all queues.  Else one wave walks a queue 64 requests at a time and settles
+//      each group by a prefix minimum, or by iterating to the fixed point where the latency table falls.
+//      Ranked variant: only the queues; ranked_queues_kernel and its like form the estimates.
 //
 // Why buckets instead of radix passes: at this data rate the vector ALU, not HBM, limits a
 // sort of 8192 keys per workgroup (about 130 lane-instructions per request at full HBM
@@ -724,8 +727,11 @@ __device__ __forceinline__ void snapshot_body(const FusedArgs& A, SnapshotLds<CA
 }
 
 // QUEUES: a kernel behind this one forms the estimates of every snapshot within the promise (ranked positions), here only the
-// queues are wanted: 3000 snapshots of up to 8000, shuffled, ranked, with the compaction 356 -> 343 us; 12,000 of up to 1000 206 ->
-// 200.  A form of its own: as a condition in the plain one it took six registers more there (spilled; 0.5 % of the plain call).
+// queues are wanted.  Ranked calls with the compaction, estimates formed and overwritten / left out: 3000 snapshots of up to 8000, shuffled,
+// 358 / 344 us (twelve stages 426 / 408, twenty of up to 4000 583 / 580), high budget first in order 320 / 304; 6000 of up to 4000
+// 313 / 302, 9000 of up to 2000 250 / 240, 12,000 of up to 1000 205 / 198, 20,000 of 300 188 / 179, 100 of 8000 79 / 78; 4096 of 8192
+// 168 / 143 for this kernel alone.  A form of its own: as a condition in the plain one it took six registers more there
+// (spilled; 0.5 % of the plain call).
 template <int T, int CAP, int SCAP, bool CONSISTENT, bool AHEAD, bool QUEUES>
 __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = CAP;
@@ -761,13 +767,13 @@ __global__ __launch_bounds__(T, 4) void fused_snapshot_kernel(FusedArgs A) {
     else snapshot_body<T, CAP, SCAP, false, CONSISTENT, AHEAD>(A, L, u, lo, m, aligned, off, results);
 }
 
-// Sequentially consistent: positions in time ahead of the walk (AHEAD) at the largest capacity, unless the snapshots fill less
-// than a quarter of it on average: then the promised bound is loose and the queues are short (12,000 snapshots of 1500 under
-// 8192, plain walk and ahead 415 and 444 us).  A snapshot takes as long as its longest queue, and how long that is only the
-// device knows.  With the compaction, shuffled, in overload: 3000 snapshots of 8000 in one queue 580 and 371 us, in three 309
-// and 274; ragged, up to 7000, six stages alike 195 and 213 (with the look), skewed 322 and 284;
-// twelve 190 and 215, skewed 351 and 321.
-// Smaller capacities: 6000 snapshots of 3500 in overload 253 and 287, 10,000 of 1000 90 and 105.
+// Sequentially consistent: positions in time for all requests first, then one prefix minimum (AHEAD), at the largest capacity, unless the
+// snapshots fill less than a quarter of it on average.  A walk takes as long as a snapshot's longest queue, the minimum does
+// not ask how the requests lie, and how they lie only the device knows: the line is a compromise.  With the compaction, shuffled, in
+// overload, walked / at once, stages alike and with most requests in few of them: 3000 snapshots of up to 7000, six stages 197 / 204
+// and 320 / 246 us, twelve 192 / 210 and 344 / 285, three alike 230 / 202; 3000 of 8000 268 / 260; 4000 of 4500 251 / 268; 6000 of 2500 under
+// 8192 277 / 313 and 403 / 353; 8000 of 1500 under 8192 280 / 303 and 364 / 321.  Smaller capacities: 6000 of 3500 254 / 271 and 405 /
+// 375, 9000 of up to 2000 155 / 174 and 258 / 261, 10,000 of 1000 130 / 136.
 template <int CAP, int T, int SCAP>
 void launch_stages(const FusedArgs& a, hipStream_t stream) {
     if constexpr (CAP == PARD_FUSED_SNAPSHOT_CAPACITY)
@@ -843,10 +849,11 @@ hipError_t launch_fused(const FusedArgs& args, hipStream_t stream) {
     // snapshot of a thousand 16.9 and 12.6 us in order, 15.9 and 14.0 shuffled; eight 19.4 and 15.1, 17.7 and 15.5; two of
     // 4000 19.5 and 18.2, 20.5 and 18.3).  The limit says what is taken for small, it is not a crossing: the difference is
     // the same at 256 snapshots of a thousand (23.1 and 19.1).  The largest capacity keeps the kernel (200 of 8000 in order
-    // 29.8 with it, 30.6 without); under sequentially consistent dropping the wide workgroups are ahead of it up to about
-    // 3000 requests a snapshot (100 snapshots in order, six stages alike / most requests in one of them, with it and
-    // without: ragged up to 4400 37.6 / 42.3 and 31.6 / 40.9, 5500 39.8 / 44.4 and 33.9 / 44.2, 8192 45.2 / 51.8 and 41.9 /
-    // 62.2).
+    // 29.8 with it, 30.6 without); under sequentially consistent dropping the wide workgroups stay ahead of it in order as well where the
+    // stages are alike (100 snapshots of 4400 36.2 with it, 29.8 without, of 6000 37.5 and 31.2, of 8192 37.0 and 30.3), and with most
+    // requests in few stages up to about 5500 (4400 36.9 and 34.6, 6000 37.8 and 38.8, 8192 37.4 and 43.0; 250 of 4400 40.0 and 37.2, 6000
+    // 41.4 and 42.2).  The line at 3072 dates from a wave per queue, whose walk the wide workgroups waited for; between it
+    // and 5500 the kernel still costs 2 to 6 us.
     const int capacity = a.cap <= 512 ? 512 : a.cap <= 1024 ? 1024 : a.cap <= 2048 ? 2048 : a.cap <= 4096 ? 4096 : 8192;
     const bool few = few_snapshots(a);
     if (tries_queue_order(a)) {

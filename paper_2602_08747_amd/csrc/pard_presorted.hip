@@ -99,9 +99,9 @@ __device__ __forceinline__ void count_request(uint32_t k, uint32_t& n0, uint32_t
 // successors come first: cost at that place plus the most any successor still takes.  The own stage's position counts the
 // earlier requests only, and what its own place in that order yields is the estimate.  Saturating 32-bit sums are enough:
 // 2^32 - 1 is past INT32_MAX as an estimate and past every deadline that can be exceeded.  Bound by vector instructions
-// (230 per request, of which about 150 here; 85 % of the issue slots).  4096 snapshots of 8192 in order, six stages: 240 us for
-// this kernel against 115 + 356 for the plain one and ranked_queues_kernel behind it, the call with the compaction 511 -> 289;
-// 12,000 of up to 1000 167 -> 151; 100 of 8000, three stages, 60 -> 32.
+// (226 per request, of which about 150 here; 193 us of issue, 0.80 of the kernel's time).  4096 snapshots of 8192 in order, six stages: 240 us for
+// this kernel against 117 + 354 for the plain one and ranked_queues_kernel behind it, the call with the compaction 510 -> 284;
+// 12,000 of up to 1000 166 -> 133; 100 of 8000 75 -> 39.
 template <int T>
 __device__ __forceinline__ void ranked_estimates(const PresortedLds<T, false, true>& L, const int S, const int sub, const int lane, uint32_t sr,
                                                  uint32_t ex0, uint32_t ex1, uint32_t ends, const uint32_t with_end,
@@ -637,7 +637,8 @@ __device__ __forceinline__ void presorted_body(const FusedArgs& A, PresortedLds<
 #define PARD_PS_WAVES 6
 #endif
 // Ranked: four (128 registers).  Six would spill a hundred of them (4096 snapshots of 8192: 534 us for the call and the compaction,
-// 289 with four).
+// 285 with four).  Sequentially consistent six, with ten registers spilled: four without a spill are slower (the same batch 234 and 258 us,
+// 3000 of up to 8000 175 and 203).
 template <int T, bool CONS, bool RANKED>
 __global__ __launch_bounds__(T, RANKED ? 4 : PARD_PS_WAVES) void presorted_snapshot_kernel(FusedArgs A) {
     constexpr int kCap = 16 * T;
@@ -686,10 +687,12 @@ __global__ __launch_bounds__(T, RANKED ? 4 : PARD_PS_WAVES) void presorted_snaps
 // requests, and below about half of that the general kernel's smaller capacities are as fast or faster (65,536
 // snapshots of 256 in queue order: 0.210 ms per call through this kernel, 0.148 through the general one; of 512:
 // 0.234 either way; 43,690 of 768: 0.181 against 0.270).  Sequentially consistent: only the largest workgroup, and
-// only where the snapshots fill more than a quarter of it on average (below that the promised bound is loose).  With the
-// compaction, six stages, in queue order / shuffled, without this kernel and with it: 3000 snapshots of 8000 in overload 240 /
-// 264 and 187 / 274 us, 4000 of 4500 245 / 263 and 215 / 276; 12,000 of 1500 under the bound 8192 438 / 444 and 505 / 474; 6000
-// of up to 3500 under their own bound gained 15 us in order and lost 12 otherwise.
+// only where the snapshots fill more than a quarter of it on average (below that the promised bound is loose).  It gains
+// where the snapshots come in order and loses its look at them where they don't, so the line is a compromise.  With the
+// compaction, six stages, in overload, without this kernel / with it, in queue order and shuffled: 3000 snapshots of 8000 237 / 185
+// and 260 / 269 us, of up to 7000 191 / 172 and 204 / 214 (most requests in few stages 228 / 172 and 246 / 256), 4000 of 4500 248 /
+// 218 and 268 / 280, 6000 of 2500 under 8192 296 / 294 and 313 / 328, 8000 of 1500 under 8192 277 / 359 and 280 / 324.  Bounds up to 4096: 6000 of
+// 3500 251 / 220 and 254 / 285, of up to 4000 207 / 208 and 209 / 236.
 bool presorted_path_covers(const FusedArgs& a) {
     if (a.consistent && (a.cap <= 4096 || a.n <= PARD_FUSED_SNAPSHOT_CAPACITY / 4 * (int64_t)a.plan.K)) return false;
     return a.todo != nullptr && a.plan.presorted_ok && a.plan.uniform_mode == PARD_ORDER_LBF &&

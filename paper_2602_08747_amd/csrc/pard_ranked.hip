@@ -8,11 +8,13 @@
 //   est = cost_k(pos) + max over the paths through k of sum over later stages i of cost_i(ahead_i(d))
 // (Section 3.2 Eq.(4) and the DAG maximum), everything else as in the plain estimate.
 //
-// It runs after the plain call, on its outputs: the queues are sorted then, so ahead_i(d) is a
+// The kernels here run behind the ones that form the queues: those are sorted then, so ahead_i(d) is a
 // binary search over queue i's slots (deadline looked up through order[]).  One thread per queue
 // slot: neighbouring threads hold neighbouring deadlines of one queue, so their searches walk the
 // same slots.  The downstream sum depends on the request now, so the path CSR is walked per
 // request; the cost of each later stage is computed once per request and kept in LDS.
+// Estimates of the plain call, where there are any, are overwritten: the on-chip kernel leaves them out for snapshots within
+// the promise, and snapshots in queue order may be finished with their ranked estimates already (RankedArgs::todo).
 #include "pard_device.hpp"
 
 namespace pard {
@@ -184,11 +186,12 @@ __global__ __launch_bounds__(kRSnapThreads) void ranked_snapshot_kernel(RankedAr
 // hands them to all.  The maximum over the paths is formed stage by stage (places rise away from the sinks) instead of
 // path by path.  A search starts from a table per queue of where every 2^shift-th deadline value of the snapshot's range
 // begins: one or two LDS steps are left of the binary search's eleven.  The table costs two bytes per bucket, a bucket
-// holds about one slot of a queue.  Snapshots in queue order don't come here where pard_presorted.hip takes them.  Saturating 32-bit sums are enough: 2^32 - 1 and everything above it is past INT32_MAX
+// holds about one slot of a queue.  Saturating 32-bit sums are enough: 2^32 - 1 and everything above it is past INT32_MAX
 // as an estimate and past every deadline that can be exceeded, even from the lowest `now`.  Bound by vector instructions
-// and dependent LDS
-// reads (about 230 and 24 per 64 slots at 6 stages).  4096 snapshots of 8192 (high budget first): 345 us, 967 with a binary search over the
-// whole queue and a walk of the paths per request (more than 16 stages still take that: ranked_snapshot_kernel).
+// and dependent LDS reads (about 230 and 24 per 64 slots at 6 stages).  4096 snapshots of 8192, in order under low budget
+// first: 354 us, 967 with a binary search over the whole queue and a walk of the paths per request (more than 16 stages still
+// take that: ranked_snapshot_kernel).  Such snapshots are finished ahead of this kernel now (todo); in order under high budget
+// first it takes 360 us, out of order 541 under either, where neighbouring slots hold requests from all over the snapshot.
 __device__ __forceinline__ uint32_t sat32(uint64_t c) { return c < 0xFFFFFFFFull ? (uint32_t)c : 0xFFFFFFFFu; }
 __device__ __forceinline__ int from_lane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 
